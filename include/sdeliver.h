@@ -160,7 +160,7 @@ typedef struct {
   int64_t spikes_emitted;    /* local spikes since creation                     */
   int64_t events_delivered;  /* synaptic events (sum of segment lengths)        */
   int64_t spikes_delivered;  /* spike entries delivered                          */
-  int64_t slices;            /* fused slice launches                            */
+  int64_t slices;            /* slices run by sd_simulate / sd_simulate_steps    */
   int64_t spikes_recorded;   /* entries in the raster                           */
   int32_t overflow;          /* sticky device flags: bit 0 spike-list overflow,  */
                              /* bit 1 raster overflow, bits 2-3 invalid entries, */
@@ -194,9 +194,8 @@ sd_status sd_build_connections(sd_ctx* ctx);
  * the current slice of d_min steps): reads and consumes the ring buffer
  * rows of those steps, draws the Poisson drive, propagates exactly, applies
  * threshold/reset/refractoriness, and appends emitted spikes to the open
- * slice's spike list (one contiguous list; each block appends its spikes in
- * (lag, neuron) order, blocks in any order - delivery sums are exact
- * integers, so the order does not change results). */
+ * slice's spike list (one contiguous list in any order - delivery sums are
+ * exact integers, so the order does not change results). */
 sd_status sd_update_neurons(sd_ctx* ctx, int32_t n_steps);
 
 /* Deliver spikes (Alg. REF result, Sec. 3.2): for every spike (src, lag) and
@@ -240,25 +239,27 @@ sd_status sd_set_count_mode(sd_ctx* ctx, int32_t on);
 /* Persistent slices (Alg. REF, Sec. 3.2, run for many slices in one
  * launch): sd_simulate / sd_simulate_steps run up to max_slices whole
  * slices per cooperative launch, one workgroup per target block.  Each
- * block keeps its ring window in LDS across the slices (window sums stay in
- * 64-bit fixed point until their step is updated) and its neurons' state in
- * registers; slices are separated by grid barriers.  The results are those
- * of the fused slices up to the FP32 rounding of the ring sums (a sum is
- * rounded once, not once per delivery).  0 switches back to one launch per
- * slice.  SD_EUNSUPPORTED unless the net is block-major, closed loop, with
+ * block keeps its ring window, the sums of steps not yet due and its
+ * neurons' state on its compute unit across the slices; between slices the
+ * blocks exchange their spikes through device memory.  The results are those
+ * of the fused slices bit for bit.  A new context runs stretches of 4 and
+ * more slices this way by itself where the net allows it (and the stream is
+ * not being captured); 0 switches to one launch per slice.
+ * SD_EUNSUPPORTED unless the net is block-major, closed loop, with
  * static synapses, blocks of a multiple of 64 and at most 1024 neurons, and
  * all blocks fit on the device at once; SD_ESTATE before
- * sd_build_connections.  A grid barrier that waits past its spin limit sets
- * bit 4 of sd_stats.overflow and ends the launch early (the run's results
- * are then invalid). */
+ * sd_build_connections.  A wait for other blocks' spikes past its spin limit
+ * sets bit 4 of sd_stats.overflow and ends the launch early (the run's
+ * results are then invalid). */
 sd_status sd_set_persistent(sd_ctx* ctx, int32_t max_slices);
 
 /* For callers that watch a persistent run (and for tests of its failure
- * path): the most polls a grid barrier of a persistent launch makes while
- * it waits for the other workgroups before it gives up, setting bit 4 of
+ * path): the most polls a workgroup of a persistent launch makes while it
+ * waits for the other workgroups' spikes before it gives up, setting bit 4 of
  * sd_stats.overflow and ending the launch early.  polls < 0 restores the
- * default of 2^22 polls; 0 makes the first workgroup to reach a barrier give
- * up at once.  SD_EINVAL for a null context. */
+ * default of 2^22 polls (2^27 in a launch that sd_set_persistent did not ask
+ * for); 0 makes the first workgroup to wait give up at once.  SD_EINVAL for a
+ * null context. */
 sd_status sd_set_barrier_spin(sd_ctx* ctx, int64_t polls);
 
 /* Open loop: precompute the virtual sources' spikes for steps

@@ -212,6 +212,18 @@ hipError_t launcher_run(SliceLauncher& L, hipStream_t s, const sd::SliceArgs* li
 
 }  // namespace
 
+constexpr int32_t kPersistAuto = -1;
+// A cooperative launch costs ~20 us more than an ordinary one and a slice in
+// it 5 to 12 us less.  At 4 slices (us, one launch per slice against
+// persistent): 1,250-neuron delta net 59.8 / 59.5, 30,011 alpha 90 / 88,
+// 112,500 packed 130 / 119, one-step slices 82 / 68; at 3 slices 45 / 50,
+// 69 / 74, 98 / 98, 61 / 59.
+constexpr int64_t kPersistAutoMin = 4;
+constexpr int64_t kPersistAutoMax = 1024;  // slices of one launch
+// a wait lasts as long as another stream's kernel keeps a block off its
+// compute unit: minutes, not the seconds of the explicit mode
+constexpr int64_t kPersistAutoSpin = 1LL << 27;
+
 struct sd_ctx {
   sd_config cfg;
   sd_sizes sz;
@@ -298,9 +310,14 @@ struct sd_ctx {
   int64_t slices = 0;
   int64_t rec_read = 0;     // raster entries already drained
   SliceLauncher lau;        // this network alone
-  int32_t persist = 0;      // slices per persistent launch (0: one launch per slice)
-  unsigned* pbar = nullptr; // grid-barrier arrivals of a persistent launch
-  int64_t bar_spin = -1;    // polls before a grid barrier gives up (< 0: default)
+  // slices per persistent launch (kPersistAuto: where it pays, 0: one launch
+  // per slice)
+  int32_t persist = kPersistAuto;
+  int persist_fit = -1;     // the plan fits and all blocks are resident (-1: not yet asked)
+  PersistPlan plan{};
+  void* xch = nullptr;      // exchange lines of a persistent launch
+  uint32_t epoch = 0;       // slices published so far (line tags, modulo 2^16)
+  int64_t bar_spin = -1;    // polls before a wait gives up (< 0: default)
 };
 
 // Independent networks advanced together: every slice of all members is
@@ -409,7 +426,7 @@ struct Layout {
   size_t off_row, off_cursor, off_seg, off_tiles, off_syn, off_dly, off_V, off_y1, off_y2, off_r,
       off_rb, off_list0, off_list1, off_cnt, off_rec, off_wte, off_wti, off_thr, off_p64, off_p32,
       off_counters, off_overflow, off_bins, off_bcnt, off_spill, off_sflag, off_ext, off_extcnt,
-      off_pmask, off_pbefore, off_aux0, off_aux1, off_prev0, off_prev1, off_pbar, total;
+      off_pmask, off_pbefore, off_aux0, off_aux1, off_prev0, off_prev1, off_xch, total;
 };
 
 constexpr size_t kLdsBudget = 160 * 1024;  // LDS of one gfx950 workgroup
@@ -574,7 +591,7 @@ sd_status make_layout(const sd_config* c, Layout* L, std::string* why) {
   L->off_p32 = take(8 * 4);
   L->off_counters = take(8 * 8);
   L->off_overflow = take(4);
-  L->off_pbar = take(4);
+  L->off_xch = take(L->sm || c->plastic ? 0 : xch_bytes(L->NB));
   const size_t brec = c->wform == SD_W_FP32 ? 8 : 4;
   L->off_bins = take(L->sm ? (size_t)L->NB * L->bin_P * L->bin_cap * brec : 0);
   L->off_bcnt = take(L->sm ? (size_t)L->NB * L->bin_P * 4 : 0);
@@ -907,7 +924,7 @@ sd_status sd_create(const sd_config* cfg, void* hip_stream, void* d_arena, size_
   c->prop32 = (float*)(A + L.off_p32);
   c->counters = (unsigned long long*)(A + L.off_counters);
   c->overflow = (int32_t*)(A + L.off_overflow);
-  c->pbar = (unsigned*)(A + L.off_pbar);
+  c->xch = A + L.off_xch;
 
   // tables (host, FP64 -> FP32 / BF16 codes)
   const sd_config& g = *cfg;
@@ -1076,6 +1093,10 @@ sd_status sd_build_connections(sd_ctx* c) {
                             c->stream));
   if (c->K > 0) HIP_TRY(c, launch_fill(c->stream, a));
   HIP_TRY(c, launch_seg_pairs(c->stream, a));
+  if (!g.plastic) {
+    HIP_TRY(c, hipMemsetAsync(c->xch, 0, xch_bytes(c->NB), c->stream));
+    c->epoch = 0;
+  }
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   uint32_t total = 0;
   HIP_TRY(c, hipMemcpy(&total, c->row + c->M - 1, 4, hipMemcpyDeviceToHost));
@@ -1271,27 +1292,91 @@ sd_status next_fused_slice(sd_ctx* c, int32_t m, SliceArgs* out) {
   *out = a;
   return SD_OK;
 }
-// S whole slices from an aligned t_now in one persistent launch; the host
-// state advances exactly as S fused slices would advance it.
-sd_status run_persistent(sd_ctx* c, int32_t S) {
+// Whether the network's blocks can run persistent slices: the plan fits the
+// LDS and all blocks are on the device at once.  Asked once per context.
+sd_status persist_fits(sd_ctx* c, bool* fits, int* occ_out = nullptr, int* n_cu_out = nullptr) {
+  const int64_t grid = 8 * (int64_t)((c->NB + 7) / 8);
+  if (c->persist_fit < 0 || occ_out) {
+    int coop = 0, n_cu = 0, occ = 0;
+    HIP_TRY(c, hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, c->device));
+    HIP_TRY(c, hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, c->device));
+    if (persist_plan(c->B, c->cfg.d_min, c->cfg.d_max, kLdsBudget - 64, &c->plan))
+      occ = persist_occupancy(c->cfg.wform, c->plan);
+    c->persist_fit = coop && c->NB <= kPersistMaxNB && (int64_t)occ * n_cu >= grid ? 1 : 0;
+    if (occ_out) *occ_out = occ;
+    if (n_cu_out) *n_cu_out = n_cu;
+  }
+  *fits = c->persist_fit == 1;
+  return SD_OK;
+}
+
+bool persist_kind(const sd_ctx* c) {
+  return !c->sm && !c->cfg.plastic && !open_loop(c->cfg) && c->B <= kSliceThreads &&
+         c->B % 64 == 0;
+}
+
+// Slices the next launch runs persistently from an aligned t_now with left
+// steps to go (0: one launch per slice).
+sd_status persist_slices(sd_ctx* c, int64_t left, int32_t* S) {
+  *S = 0;
+  const int32_t Dmin = c->cfg.d_min;
+  if (c->persist == 0 || left < Dmin) return SD_OK;
+  if (c->pend_open && c->pend_t0 + Dmin != c->t_now) return SD_OK;
+  // ring rows past the carried ones (an external list delivered ahead)
+  if (c->rb_hi > c->t_now + c->cfg.d_max - Dmin) return SD_OK;
+  int64_t n = left / Dmin;
+  if (c->persist == kPersistAuto) {
+    n = std::min<int64_t>(n, kPersistAutoMax);
+    if (n < kPersistAutoMin || !persist_kind(c)) return SD_OK;
+    // a cooperative launch is not recorded into a caller's graph; where the
+    // question itself is refused (the null stream while another stream is
+    // captured), neither is it made
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess) {
+      (void)hipGetLastError();
+      return SD_OK;
+    }
+    if (cs != hipStreamCaptureStatusNone) return SD_OK;
+    bool fits = false;
+    sd_status s = persist_fits(c, &fits);
+    if (s != SD_OK || !fits) return s;
+  } else {
+    n = std::min<int64_t>(n, c->persist);
+  }
+  *S = (int32_t)n;
+  return SD_OK;
+}
+
+// S whole slices from an aligned t_now in one persistent launch.  The last
+// slice's spikes go to the list counter after the open one whatever S is;
+// the lists alternate per slice.
+// *done stays false where the runtime refuses a launch that nobody asked for:
+// the net then runs one launch per slice.
+sd_status run_persistent(sd_ctx* c, int32_t S, bool* done) {
   const sd_config& g = c->cfg;
   const int32_t Dmin = g.d_min;
-  SliceArgs a = base_args(c);
-  a.in_cap = c->list_cap;
-  a.zero_cnt = nullptr;
-  const int32_t pend0 = c->pend_open ? 1 : 0;
-  HIP_TRY(c, launch_set_word(c->stream, c->pbar, 0u));  // the grid barrier's arrival counter
-  HIP_TRY(c, launch_persist(c->stream, a, c->list, c->cnt3, c->cur, c->ci, pend0, S, c->t_now,
-                            c->rb_hi, c->pbar, c->bar_spin, c->lau.lds, g.wform));
-  for (int32_t k = 0; k < S; ++k) {
-    if (k > 0 || pend0) c->rb_hi = std::max(c->rb_hi, c->t_now + g.d_max);
-    c->cur ^= 1;
-    c->ci = (c->ci + 1) % 3;
-    c->pend_open = true;
-    c->pend_t0 = c->t_now;
-    c->t_now += Dmin;
-    c->slices += 1;
+  const SliceArgs a = base_args(c);
+  const int64_t spin = c->bar_spin >= 0 ? c->bar_spin
+                       : c->persist == kPersistAuto ? kPersistAutoSpin : -1;
+  *done = false;
+  const hipError_t e =
+      launch_persist(c->stream, a, c->list, c->cnt3, c->cur, c->ci, c->pend_open ? 1 : 0, S,
+                     c->t_now, c->rb_hi, c->xch, c->epoch + 1, spin, c->plan, g.wform);
+  if (e != hipSuccess && c->persist == kPersistAuto) {
+    (void)hipGetLastError();
+    c->persist_fit = 0;
+    return SD_OK;
   }
+  HIP_TRY(c, e);
+  *done = true;
+  c->epoch += (uint32_t)S;
+  c->cur ^= S & 1;
+  c->ci = (c->ci + 1) % 3;
+  c->pend_open = true;
+  c->t_now += (int64_t)S * Dmin;
+  c->pend_t0 = c->t_now - Dmin;
+  c->rb_hi = std::max(c->rb_hi, c->t_now + g.d_max - Dmin);
+  c->slices += S;
   return SD_OK;
 }
 }  // namespace
@@ -1306,21 +1391,19 @@ sd_status sd_set_persistent(sd_ctx* c, int32_t max_slices) {
     return SD_OK;
   }
   if (!c->built) return fail(c, SD_ESTATE, "build_connections first");
-  const sd_config& g = c->cfg;
-  if (c->sm || g.plastic || open_loop(g))
+  if (c->sm || c->cfg.plastic || open_loop(c->cfg))
     return fail(c, SD_EUNSUPPORTED,
                 "persistent slices need a block-major, closed-loop net with static synapses");
-  if (c->B > kSliceThreads || c->B % 64 != 0)
+  if (!persist_kind(c))
     return fail(c, SD_EUNSUPPORTED, "persistent slices need blocks of a multiple of 64 and at "
                 "most %d neurons", kSliceThreads);
-  int coop = 0, n_cu = 0;
-  HIP_TRY(c, hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, c->device));
-  HIP_TRY(c, hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, c->device));
-  const int64_t grid = 8 * (int64_t)((c->NB + 7) / 8);
-  const int occ = persist_occupancy(g.wform, c->lau.lds);
-  if (!coop || (int64_t)occ * n_cu < grid)
+  bool fits = false;
+  int occ = 0, n_cu = 0;
+  sd_status s = persist_fits(c, &fits, &occ, &n_cu);
+  if (s != SD_OK) return s;
+  if (!fits)
     return fail(c, SD_EUNSUPPORTED, "persistent slices need all %lld blocks resident at once "
-                "(%d per CU on %d CUs)", (long long)grid, occ, n_cu);
+                "(%d per CU on %d CUs)", (long long)(8 * (int64_t)((c->NB + 7) / 8)), occ, n_cu);
   c->persist = max_slices;
   return SD_OK;
 }
@@ -1355,19 +1438,21 @@ sd_status sd_simulate_steps(sd_ctx* c, int64_t n_steps) {
       left -= m;
       continue;
     }
-    if (c->persist > 0 && left >= Dmin && (!c->pend_open || c->pend_t0 + Dmin == c->t_now)) {
-      const int32_t S = (int32_t)std::min<int64_t>(left / Dmin, c->persist);
-      sd_status s = flush();
-      if (s == SD_OK) s = run_persistent(c, S);
-      if (s != SD_OK) return s;
-      left -= (int64_t)S * Dmin;
-      continue;
+    int32_t S = 0;
+    sd_status s = persist_slices(c, left, &S);
+    if (s == SD_OK && S > 0) {
+      s = flush();
+      bool done = false;
+      if (s == SD_OK) s = run_persistent(c, S, &done);
+      if (done) left -= (int64_t)S * Dmin;
     }
+    if (s != SD_OK) return s;
+    if (S > 0) continue;
     const int32_t m = (int32_t)std::min<int64_t>(left, Dmin);
     SliceArgs a;
     // source-major: the binning launch is issued inside next_fused_slice,
     // so queued slices go first and this slice right after it
-    sd_status s = c->sm ? flush() : SD_OK;
+    if (c->sm) s = flush();
     if (s == SD_OK) s = next_fused_slice(c, m, &a);
     if (s != SD_OK) {
       flush();

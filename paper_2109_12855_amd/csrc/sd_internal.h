@@ -207,11 +207,21 @@ hipError_t launch_slice(hipStream_t s, const SliceArgs* d_args, const int2* d_ma
                         int32_t n_blocks, size_t lds, int wform);
 // one fused slice of a single network, arguments by value
 hipError_t launch_slice1(hipStream_t s, const SliceArgs& a, size_t lds, int wform);
-int persist_occupancy(int wform, size_t lds);
+// persistent slices: LDS plan of a block size, and one launch of S slices
+struct PersistPlan {
+  bool carry_lds;   // sums of later steps in LDS (else in the HBM ring)
+  int32_t drows;    // drive-count rows
+  int32_t cap;      // spikes per walk chunk
+  size_t lds;
+};
+constexpr int kPersistMaxNB = 512;  // two 1024-thread workgroups per compute unit
+bool persist_plan(int32_t B, int32_t Dmin, int32_t Dmax, size_t budget, PersistPlan* plan);
+size_t xch_bytes(int32_t NB);  // exchange lines of NB blocks
+int persist_occupancy(int wform, const PersistPlan& plan);
 hipError_t launch_persist(hipStream_t s, const SliceArgs& a, uint32_t* const lists[2],
                           int32_t* cnt3, int32_t cur0, int32_t ci0, int32_t pend0, int32_t S,
-                          int64_t t0, int64_t rb_hi0, unsigned* bar, int64_t spin_limit,
-                          size_t lds, int wform);
+                          int64_t t0, int64_t rb_hi0, void* xch, uint32_t epoch0,
+                          int64_t spin_limit, const PersistPlan& plan, int wform);
 size_t slice_lds_bytes(int B, int Dmin, int win_rows, bool plastic = false, bool bin = false);
 // add shift to the time fields (t_upd, t_slice0, w_lo, rb_hi) of args[0..n)
 hipError_t launch_shift_args(hipStream_t s, SliceArgs* args, int32_t n, int64_t shift);
@@ -222,7 +232,6 @@ hipError_t launch_fill_sm(hipStream_t s, const BuildArgs& a);
 hipError_t launch_bin(hipStream_t s, const BinArgs& a, int32_t P, size_t lds, bool w8);
 hipError_t launch_zero_rows(hipStream_t s, float* rb, int64_t N, int32_t L, int64_t t_lo,
                             int64_t t_hi);
-hipError_t launch_set_word(hipStream_t s, unsigned* p, unsigned v);
 // pack and validate an external spike list (see k_pack_list); cnt receives n
 hipError_t launch_pack_list(hipStream_t s, const uint32_t* src, const uint8_t* lag, int64_t n,
                             int64_t n_src, int32_t Dmin, uint32_t* out, int32_t* cnt,

@@ -18,9 +18,9 @@
 //   a time; the slice kernel then accumulates those instead of walking
 //   segments (k_slice1<form, true, dyn>).
 //   k_shift_args moves the device-resident arguments of a captured batch
-//   graph on by one period.  k_persist (opt-in) runs several slices in one
-//   cooperative launch, each block's ring window kept in LDS across them,
-//   with grid barriers between slices.
+//   graph on by one period.  k_persist runs several slices in one cooperative
+//   launch, each block's ring window kept in LDS across them, the spikes
+//   exchanged through device memory between slices.
 //
 // Build (once, untimed, Sec. 2.2):
 //   k_count / scan / k_fill lay out the block-major table: segment (src, b)
@@ -876,6 +876,33 @@ __device__ __forceinline__ float from_fixed(long long q, float inv) {
   return (float)q * inv;
 }
 
+// Poisson-drive counts of one Philox block's eight 32-bit uniforms: the number
+// of the n_thr ascending thresholds at or below each.  The table (LDS, padded
+// to kMaxThr with 2^32 - 1) is read four thresholds at a time, one broadcast
+// for all eight uniforms, until no lane's largest uniform reaches further: a
+// uniform searched by itself waits for an LDS read per threshold.  A uniform
+// of 2^32 - 1 counts padding too, hence the bound.
+__device__ __forceinline__ void drive_counts(const uint64_t rr[4], const uint32_t* thr, int n_thr,
+                                             uint32_t cnt[8]) {
+  uint32_t u[8], top = 0u;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    u[q] = (q & 1) ? (uint32_t)(rr[q >> 1] >> 32) : (uint32_t)rr[q >> 1];
+    top = u[q] > top ? u[q] : top;
+    cnt[q] = 0u;
+  }
+  for (int i = 0; i < n_thr; i += 4) {
+    const uint4 t = ((const uint4*)thr)[i >> 2];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      cnt[q] += (uint32_t)(u[q] >= t.x) + (uint32_t)(u[q] >= t.y) + (uint32_t)(u[q] >= t.z) +
+                (uint32_t)(u[q] >= t.w);
+    if (!__any(top >= t.w)) break;
+  }
+#pragma unroll
+  for (int q = 0; q < 8; ++q) cnt[q] = cnt[q] < (uint32_t)n_thr ? cnt[q] : (uint32_t)n_thr;
+}
+
 template <bool V> struct BoolC { static constexpr bool value = V; };
 
 // A thread keeps the staged HBM ring rows of its own neuron in registers
@@ -957,6 +984,79 @@ __device__ __forceinline__ float plastic_walk(const SliceArgs& a, float w, int d
     tprev = t_pre;
   }
   return w;
+}
+
+// Waves take groups of G segments of the n_c spikes described in desc / meta
+// from a shared counter until the chunk is done (a wave slowed by issue
+// priority or memory latency simply takes fewer groups), and add every
+// synapse's fixed-point weight into the ring window.  G loads issue back to
+// back (lanes past a segment's end and slots past the chunk read record 0,
+// unused), then the adds; the group bound is uniform.
+template <int WF>
+__device__ __forceinline__ void walk_chunk(const SliceArgs& a, const uint2* desc,
+                                           const uint32_t* meta, int n_c, int* s_next,
+                                           long long* win, int32_t j0, int Dmin, int B, int lane) {
+  constexpr int G = SynGroup<WF>::n;
+  for (;;) {
+    int g0 = 0;
+    if (lane == 0)
+      g0 = __hip_atomic_fetch_add(s_next, G, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    g0 = __builtin_amdgcn_readfirstlane(g0);
+    if (g0 >= n_c) break;
+    const int n_here = (n_c - g0) < G ? (n_c - g0) : G;
+    SynRaw<WF> raw[G];
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const uint2 d = desc[g0 + u];  // past the chunk: stale or padding, masked
+      const bool on = (u < n_here) & (lane < (int)d.y) & (d.x != 0xffffffffu);
+      raw[u] = syn_fetch<WF>(a.syn, a.syn_dly, on ? d.x + (uint32_t)lane : 0u);
+    }
+    uint32_t mt[G];
+    bool any_long = false;
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      mt[u] = meta[g0 + u];
+      any_long |= (mt[u] & 127u) > 64u;  // unconditional use: no sinking
+    }
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const uint32_t m = __builtin_amdgcn_readfirstlane(mt[u]);
+      const uint32_t sel = (uint32_t)((int32_t)m >> 31);  // all ones: inhibitory
+      const float m0 = __uint_as_float((__float_as_uint(a.wm0_e) & ~sel) |
+                                       (__float_as_uint(a.wm0_i) & sel));
+      const float m1 = __uint_as_float((__float_as_uint(a.wm1_e) & ~sel) |
+                                       (__float_as_uint(a.wm1_i) & sel));
+      long long* row = win + ((m >> 7) & 0xffffffu);
+      if ((u < n_here) & (lane < (int)(m & 127u))) {
+        int slot, v;
+        syn_decode<WF>(raw[u], j0, Dmin, B, m0, m1, slot, v);
+        __hip_atomic_fetch_add((unsigned long long*)&row[slot], (unsigned long long)(long long)v,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+    // segments longer than one wave
+    if (__builtin_amdgcn_readfirstlane((int)any_long)) {
+      for (int u = 0; u < n_here; ++u) {
+        const uint2 d = desc[g0 + u];
+        const uint32_t m = meta[g0 + u];
+        const int sl = __builtin_amdgcn_readfirstlane((int)d.y);
+        const bool inh = (int)m < 0;
+        for (int e0 = 64; e0 < sl; e0 += 64) {
+          const bool on = lane + e0 < sl;
+          const SynRaw<WF> x =
+              syn_fetch<WF>(a.syn, a.syn_dly, on ? d.x + (uint32_t)(e0 + lane) : 0u);
+          if (on) {
+            int slot, v;
+            syn_decode<WF>(x, j0, Dmin, B, inh ? a.wm0_i : a.wm0_e, inh ? a.wm1_i : a.wm1_e,
+                           slot, v);
+            __hip_atomic_fetch_add((unsigned long long*)&win[(int)((m >> 7) & 0xffffffu) + slot],
+                                   (unsigned long long)(long long)v, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+          }
+        }
+      }
+    }
+  }
 }
 
 // One workgroup's slice for target block b of the network described by a.
@@ -1781,98 +1881,154 @@ __global__ void __launch_bounds__(kSliceThreads) k_slice1(SingleArgs s) {
 // persistent multi-slice kernel (block-major, static synapses, closed loop)
 // ---------------------------------------------------------------------------
 // One cooperative launch runs S consecutive fused slices of a network whose
-// blocks are all resident at once (one workgroup per block).  A workgroup
-// keeps its block's delivery window in LDS for the whole launch, as a ring
-// of Dmax rows indexed by step modulo Dmax: a delivery adds into the rows of
-// steps [w_lo, w_lo + Dmax) (Alg. REF, Sec. 3.2), the update reads the rows
-// of its steps and clears them for reuse, and only at the end do the rows
-// due after the last slice go to the HBM ring.  Window sums therefore stay
-// in fixed point until their step is updated.  Neuron state stays in
-// registers.  Slices are separated by a grid barrier, since the spike list
-// one slice writes is read by every block in the next; the lists and their
-// three rotating counters are those of the one-launch-per-slice path.
-constexpr int64_t kBarSpin = 1LL << 22;  // default polls before a grid barrier gives up
+// blocks are all resident at once (one workgroup per block).  Per slice a
+// workgroup collects the spikes of all blocks, walks their segments into its
+// ring window (Alg. REF, Sec. 3.2), updates its neurons and publishes its own
+// new spikes.  The window, the FP32 sums of steps not yet due (carry, one
+// rounding per delivery as in the ring of the one-launch-per-slice path, so
+// results are the same bit for bit) and the neuron state stay on the compute
+// unit.
+//
+// What bounds a short slice is its chain of dependent memory round trips, so
+// the exchange is one: every block owns a line of kXchWords 64-bit words per
+// slice parity, each word a 16-bit slice tag with up to three 16-bit spikes
+// (word 0: the block's spike count and two spikes), written by one wave with
+// relaxed agent-scope atomic stores.  A reader polls a word until its tag is
+// the slice's: tag and payload are one atomic word, so no word needs ordering
+// against another and no cache is written back or invalidated (a counter
+// barrier around the same exchange took 9.9 us, mostly the two fences).  All
+// words of a line are rewritten every slice, so a stale word's tag is that of
+// two slices before.  A line is reused two slices later: its writer has by
+// then read every block's line of the slice between, which each block writes
+// after its last read of this one.  Spikes past a line's capacity go to the
+// block's part of the slice's list buffer, between a release and an acquire
+// fence.
+// Per slice, one launch per slice against this kernel (stretches of 20 to 100
+// slices): 1,250-neuron delta net 14.9 -> 9.6 us, 30,011 alpha neurons 22.5 ->
+// 15, 112,500 packed 32.8 -> 22.5, FP32 37.6 -> 28, one-step slices 20.5 ->
+// 8.6.
+constexpr int64_t kBarSpin = 1LL << 22;  // polls before a wait gives up (explicit mode)
+constexpr int kXchWords = 32;            // 64-bit words of a block's line
+constexpr int kXchPoll = 4;              // words of a line read by the first poll
+constexpr int kXchMax = 2 + 3 * (kXchWords - 1);  // spikes a line holds
+constexpr int kXchFirst = 2 + 3 * (kXchPoll - 1); // spikes the first poll reads
+constexpr int kPubCap = 1024;            // spikes of a slice a block holds in LDS
 
-// All workgroups of the launch wait here; the release fence publishes this
-// workgroup's global writes (spike list, counters) and the acquire fence
-// drops stale lines of other workgroups' writes.  A wait past spin_limit polls
-// sets bit 4 of the overflow flags, and every workgroup then leaves.
-__device__ bool grid_barrier(unsigned* bar, unsigned target, int32_t* overflow,
-                             int64_t spin_limit) {
-  __shared__ int s_ok;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __hip_atomic_fetch_add(bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    int64_t spins = 0;
-    int ok = 1;
-    while (__hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-      __builtin_amdgcn_s_sleep(1);
-      if ((++spins & 255) == 0 &&
-          (__hip_atomic_load(overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 16)) {
-        ok = 0;
-        break;
-      }
-      if (spins > spin_limit) {
-        atomicOr(overflow, 16);
-        ok = 0;
-        break;
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    s_ok = ok;
-  }
-  __syncthreads();
-  return s_ok != 0;
-}
+size_t xch_bytes(int32_t NB) { return (size_t)2 * NB * kXchWords * 8; }
 
 struct PersistArgs {
-  SliceArgs a;         // network constants; time and list fields of slice 0
+  SliceArgs a;         // network constants
   uint32_t* lists[2];  // the two spike-list buffers
   int32_t* cnt3;       // the three rotating list counters
   int32_t cur0, ci0;   // slice 0 reads lists[cur0] with count cnt3[ci0]
   int32_t pend0;       // slice 0 delivers that list (else no delivery)
   int32_t S;           // slices
   int32_t per_xcd;     // blocks per XCD (grid = 8 * per_xcd)
+  int32_t cap;         // spikes per walk chunk
+  int32_t drows;       // drive-count rows (d_min, or whole 8-step chunks)
+  uint32_t epoch0;     // tag of slice 0's line
   int64_t t0;          // first step of slice 0
   int64_t rb_hi0;      // HBM ring rows of steps below this hold earlier sums
-  unsigned* bar;       // grid-barrier arrivals (zero at launch)
-  int64_t spin_limit;  // polls before a grid barrier gives up
+  uint64_t* xch;       // exchange lines [2][NB][kXchWords]
+  int64_t spin_limit;  // polls before a wait gives up
 };
 
-template <int WF>
+// LDS layout of a persistent workgroup
+struct PersistLds {
+  size_t win, carry, dcnt, thr, pub, desc, meta, total;
+};
+__host__ __device__ inline PersistLds persist_lds_layout(int B, int Dmin, int Dmax, int drows,
+                                                         bool carry_lds, int cap) {
+  auto up = [](size_t x) { return (x + 15) / 16 * 16; };
+  PersistLds L;
+  size_t o = 0;
+  L.win = o;   o = up(o + (size_t)Dmax * B * 8);
+  L.carry = o; o = up(o + (carry_lds ? (size_t)(Dmax - Dmin) * B * 4 : 0));
+  L.dcnt = o;  o = up(o + (size_t)drows * B);
+  L.thr = o;   o = up(o + (size_t)kMaxThr * 4);
+  L.pub = o;   o = up(o + (size_t)kPubCap * 2);
+  L.desc = o;  o = up(o + (size_t)(cap + kMaxGroup) * 8);
+  L.meta = o;  o = up(o + (size_t)(cap + kMaxGroup) * 4);
+  L.total = o;
+  return L;
+}
+
+// The largest configuration that fits the LDS: carry rows in LDS before the
+// HBM ring, drive counts kept for whole 8-step chunks before recomputed per
+// slice, then as many spikes per walk chunk as fit (at most 2048).
+bool persist_plan(int32_t B, int32_t Dmin, int32_t Dmax, size_t budget, PersistPlan* plan) {
+  const int32_t ring = (Dmin + 14) / 8 * 8;
+  for (int k = 0; k < 4; ++k) {
+    PersistPlan p;
+    p.carry_lds = (k & 1) == 0;
+    p.drows = (k & 2) == 0 ? ring : Dmin;
+    const size_t base = persist_lds_layout(B, Dmin, Dmax, p.drows, p.carry_lds, 0).total;
+    const size_t least = persist_lds_layout(B, Dmin, Dmax, p.drows, p.carry_lds, 256).total;
+    if (least > budget) continue;
+    p.cap = (int32_t)std::min<size_t>(2048, (budget - base - 32) / 12 / 64 * 64);
+    p.cap = std::max(p.cap, 256);
+    p.lds = persist_lds_layout(B, Dmin, Dmax, p.drows, p.carry_lds, p.cap).total;
+    *plan = p;
+    return true;
+  }
+  return false;
+}
+
+// The code of a slice runs once per slice, so its size counts: unrolled to
+// ~70 KB it ran from the L2 through the 64 KB instruction cache that two
+// compute units share (~0.8 us per step of the update).  The update and the
+// flush are therefore loops over rows with the next row's reads in flight,
+// and spikes are collected as a mask of steps per neuron and listed in one
+// loop after the update.
+template <int WF, bool CL>
 __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
   const PersistArgs* pp = (const PersistArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  touch_lines(pp);
   const SliceArgs& a = pp->a;
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  constexpr int nwv = kSliceThreads / 64;
   const int gx = blockIdx.x;
   const int b = (gx & 7) * pp->per_xcd + (gx >> 3);
-  const bool live = b < a.NB;  // padding workgroups only take part in the barriers
-  const int B = a.B, Dmin = a.Dmin, R = a.Dmax, NB = a.NB;
-  const int RB = R * B;
-  const int64_t j0 = (int64_t)(live ? b : 0) * B;
-  const int nb = live ? (int)((a.N - j0) < B ? (a.N - j0) : B) : 0;
-  const int Wd = B >> 5;
-  const SliceLds Lo = slice_lds_layout(B, Dmin, R);
+  const int NB = a.NB;
+  if (b >= NB) return;
+  const int B = a.B, Dmin = a.Dmin, Dmax = a.Dmax, R = Dmax - Dmin;
+  const int CAP = pp->cap, drows = pp->drows;
+  const bool dring = drows != Dmin;  // drive counts kept for whole chunks, row t % drows
+  const int64_t N = a.N;
+  const int64_t j0 = (int64_t)b * B;
+  const int nb = (int)((N - j0) < B ? (N - j0) : B);
+  const PersistLds Lo = persist_lds_layout(B, Dmin, Dmax, drows, CL, CAP);
   long long* win = (long long*)(lds_raw + Lo.win);
+  float* carry = (float*)(lds_raw + Lo.carry);
   uint8_t* dcnt = lds_raw + Lo.dcnt;
-  uint32_t* mask = (uint32_t*)(lds_raw + Lo.mask);
   uint32_t* thr = (uint32_t*)(lds_raw + Lo.thr);
-  int32_t* scr = (int32_t*)(lds_raw + Lo.scr);
+  uint16_t* pub = (uint16_t*)(lds_raw + Lo.pub);
   uint2* desc = (uint2*)(lds_raw + Lo.desc);
   uint32_t* meta = (uint32_t*)(lds_raw + Lo.meta);
-  __shared__ int s_next, s_base;
-  __shared__ unsigned long long s_rbase, s_ev;
+  __shared__ int s_next, s_tot, s_cnt, s_abort;
+  __shared__ unsigned long long s_ev;
 
-  for (int i = tid; i < RB; i += kSliceThreads) win[i] = 0;
-  if (tid < kMaxThr) thr[tid] = (tid < a.n_thr) ? a.thr[tid] : 0xffffffffu;
-  if (tid == 0) s_ev = 0;
-  // neuron state of this thread's neuron, in registers for the launch
+  const int64_t t0 = pp->t0;
+  const int n_thr = a.n_thr;
+  for (int i = tid; i < Dmax * B; i += kSliceThreads) win[i] = 0;
+  if (tid < kMaxThr) thr[tid] = (tid < n_thr) ? a.thr[tid] : 0xffffffffu;
+  if (tid == 0) {
+    s_tot = 0;
+    s_cnt = 0;
+    s_abort = 0;
+    s_ev = 0;
+  }
+  // the list counter after the one this launch appends to
+  if (b == 0 && tid == 0) pp->cnt3[(pp->ci0 + 2) % 3] = 0;
+  // this thread's neuron: state in registers, sums of earlier deliveries in
+  // LDS (CL) or left in the HBM ring, rows not yet written cleared
   const bool own = tid < nb;
   const int64_t gn = j0 + (own ? tid : 0);
   float V = 0.f, y1 = 0.f, y2 = 0.f;
   int rf = 0;
+  int cb = R > 0 ? (int)(t0 % R) : 0;  // carry row of step w_lo
+  int lb = (int)(t0 % a.L);            // HBM ring row of step w_lo
   if (own) {
     V = a.V[gn];
     rf = a.r[gn];
@@ -1880,233 +2036,419 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
       y1 = a.y1[gn];
       y2 = a.y2[gn];
     }
+    for (int q = 0; q < R; ++q) {
+      int lr = lb + q, row = cb + q;
+      if (lr >= a.L) lr -= a.L;
+      if (row >= R) row -= R;
+      float* cell = a.rb + (int64_t)lr * N + gn;
+      if constexpr (CL) carry[row * B + tid] = t0 + q < pp->rb_hi0 ? *cell : 0.f;
+      else if (t0 + q >= pp->rb_hi0) *cell = 0.f;
+    }
   }
-  const float P11 = a.prop[0], P21 = a.prop[1], P22 = a.prop[2], P31 = a.prop[3];
-  const float P32 = a.prop[4], P33 = a.prop[5], P30Ie = a.prop[6], insc = a.prop[7];
-  const float inv = a.fx_inv, drive_w = a.drive_w;
-  const float e_l = a.e_l, v_th = a.v_th, v_reset = a.v_reset;
-  const int ref_steps = a.ref_steps;
-  const bool delta = a.model == MODEL_DELTA;
-  float m0e = a.wm0_e, m0i = a.wm0_i, m1e = a.wm1_e, m1i = a.wm1_i;
-  asm volatile("" : "+s"(m0e), "+s"(m0i), "+s"(m1e), "+s"(m1i));
-  unsigned long long spk_all = 0, in_all = 0;
-  const int64_t t0 = pp->t0, rb_hi0 = pp->rb_hi0;
+  unsigned long long spk_all = 0, in_all = 0, ev = 0;
   const int S = pp->S;
-  int cur = pp->cur0, ci = pp->ci0;
-  bool ok = true;
-  __syncthreads();  // window, thresholds
+  const float inv = a.fx_inv;
 
+  // Philox drive counts of a slice's steps: one block per (neuron, 8-step
+  // chunk); a chunk that reaches past the slice is kept for the next one
+  // (dring) or drawn again.  Groups of nb threads take a chunk each.
+  const int dgrp = kSliceThreads / nb;
+  const int dsub = tid / nb, dn = tid - dsub * nb;
+  int64_t chunk_done = (t0 >> 3) - 1;      // chunks drawn so far (dring)
+  int db = dring ? (int)(t0 % drows) : 0;  // drive-count row of step w_lo
+
+  // one spike at a position of the walk chunk: descriptor of its segment in
+  // this block
+  auto put = [&](int pos, uint2 sg, uint32_t src, int lag) {
+    desc[pos] = sg;
+    meta[pos] = ((uint32_t)(lag * B) << 7) | (sg.y < 65u ? sg.y : 65u) |
+                (((int64_t)src >= a.src_e_end) ? 0x80000000u : 0u);
+    ev += (unsigned long long)sg.y;
+  };
+  // the spikes of one word of block blk's line (spike `first` on), of which
+  // the first cnt exist, at positions at, at + 1, ...; those outside the walk
+  // chunk are skipped
+  auto put_word = [&](uint64_t w, int blk, int first, int n, int cnt, int at) {
+    uint2 sg[3];
+    bool on[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      on[i] = i < n && first + i < cnt && at + i >= 0 && at + i < CAP;
+      const uint32_t e = (uint32_t)(w >> (16 * i)) & 0xffffu;
+      const uint32_t src = (uint32_t)blk * (uint32_t)B + (e & 1023u);
+      sg[i] = a.seg[on[i] ? (uint64_t)src * (uint32_t)NB + (uint32_t)b : 0ull];
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const uint32_t e = (uint32_t)(w >> (16 * i)) & 0xffffu;
+      if (on[i]) put(at + i, sg[i], (uint32_t)blk * (uint32_t)B + (e & 1023u), (int)(e >> 10));
+    }
+  };
+  // a wait past the limit, or another workgroup's, ends the launch
+  auto give_up = [&](int64_t spins) {
+    if (spins <= pp->spin_limit &&
+        ((spins & 255) != 0 ||
+         !(__hip_atomic_load(a.overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 16)))
+      return false;
+    if (lane == 0) {
+      atomicOr(a.overflow, 16);
+      s_abort = 1;
+    }
+    return true;
+  };
+
+  int wbase[kPersistMaxNB / 256] = {};  // this wave's first list positions
+  int cur = pp->cur0;
+  bool ok = true;
+  __syncthreads();  // window, thresholds, counters
   for (int k = 0; k < S && ok; ++k) {
     const int64_t w_lo = t0 + (int64_t)k * Dmin;  // first step of slice k
-    const bool deliver = k > 0 || pp->pend0;
-    const uint32_t* in_list = pp->lists[cur];
-    int32_t* in_cnt = pp->cnt3 + ci;
-    uint32_t* out_list = pp->lists[cur ^ 1];
-    int32_t* out_cnt = pp->cnt3 + (ci + 1) % 3;
-    // the counter of slice k + 1's list starts at zero; its last reader was
-    // slice k - 1's delivery, before the barrier
-    if (gx == 0 && tid == 0) __hip_atomic_store(pp->cnt3 + (ci + 2) % 3, 0, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-    for (int i = tid; i < Dmin * Wd; i += kSliceThreads) mask[i] = 0u;
-    // ---- drive counts of the slice's steps (Philox, as in the fused slice)
+    const uint32_t tag = (pp->epoch0 + (uint32_t)k) & 0xffffu;  // of this slice's spikes
+    uint32_t* const ilist = pp->lists[cur];
+    uint32_t* const olist = pp->lists[cur ^ 1];
+    // ---- drive counts (while the other blocks' lines arrive) ---------------
     {
-      const int64_t c0 = w_lo >> 3, c1 = (w_lo + Dmin - 1) >> 3;
-      const int n_tasks = live ? (int)(c1 - c0 + 1) * nb : 0;
-      for (int task = tid; task < n_tasks; task += kSliceThreads) {
-        const int n = task % nb;
-        const int64_t c = c0 + task / nb;
-        uint64_t rr[4];
-        philox(a.seed, STREAM_DRIVE, (uint64_t)(j0 + n), (uint64_t)c, rr);
+      const int64_t c1 = (w_lo + Dmin - 1) >> 3;
+      const int64_t c0 = dring ? chunk_done + 1 : w_lo >> 3;
+      const int n_ch = (int)(c1 - c0 + 1), row0 = db + (int)(c0 * 8 - w_lo);
+      chunk_done = c1;
+      if (dsub < dgrp) {
+        for (int ci = dsub; ci < n_ch; ci += dgrp) {
+          uint64_t rr[4];
+          uint32_t cnt[8];
+          philox(a.seed, STREAM_DRIVE, (uint64_t)(j0 + dn), (uint64_t)(c0 + ci), rr);
+          drive_counts(rr, thr, n_thr, cnt);
+          int row = row0 + ci * 8;
+          if (dring)
+            while (row >= drows) row -= drows;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const int64_t t = c * 8 + q;
-          if (t < w_lo || t >= w_lo + Dmin) continue;
-          const uint64_t word = rr[q >> 1];
-          const uint32_t u = (q & 1) ? (uint32_t)(word >> 32) : (uint32_t)word;
-          int cnt = 0;
-          while (cnt < a.n_thr && u >= thr[cnt]) ++cnt;
-          dcnt[(int)(t - w_lo) * B + n] = (uint8_t)cnt;
+          for (int q = 0; q < 8; ++q)
+            if (dring || (row + q >= 0 && row + q < Dmin))
+              dcnt[(row + q) * B + dn] = (uint8_t)cnt[q];
         }
       }
     }
-    // ---- delivery of the previous slice's spikes into the window ring ----
-    if (deliver && live) {
-      constexpr int G = SynGroup<WF>::n;
-      const int base = (int)(w_lo % R);  // ring row of step w_lo
-      int64_t total = __hip_atomic_load(in_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (total > a.in_cap) total = a.in_cap;  // overflow is flagged by the writer
-      uint64_t ev = 0;
-      for (int64_t c0 = 0; c0 < total; c0 += kSliceThreads) {
-        const int n_c = (int)((total - c0) < kSliceThreads ? (total - c0) : kSliceThreads);
-        __syncthreads();  // the previous chunk's descriptors are no longer read
-        if (tid < n_c) {
-          const uint32_t ent = in_list[c0 + tid];
+    // ---- delivery of the slice before into the window ---------------------
+    int64_t total = 0;
+    if (k == 0 && pp->pend0) {
+      total = pp->cnt3[pp->ci0];
+      if (total > a.out_cap) total = a.out_cap;  // overflow is flagged by the writer
+    }
+    for (int64_t c0 = 0;; c0 += CAP) {
+      if (tid == 0) s_next = 0;
+      if (k > 0) {
+        // Spikes of every block's line, as descriptors of the positions [c0,
+        // c0 + CAP); the first round waits for the lines and counts the
+        // spikes into s_tot.  16 lines per wave, words 0..3 one per lane.
+        const uint32_t tag_in = (tag - 1u) & 0xffffu;
+        const uint64_t* xin = pp->xch + (size_t)(tag_in & 1u) * NB * kXchWords;
+        if (pp->spin_limit == 0) give_up(1);  // no polls allowed
+        int gi = 0;
+#pragma unroll 1
+        for (int g = wv * 16; g < NB; g += nwv * 16, ++gi) {
+          const int blk = g + (lane >> 2), kw = lane & 3;
+          const bool has = blk < NB;
+          const uint64_t* line = xin + (size_t)(has ? blk : 0) * kXchWords;
+          uint64_t w = (uint64_t)tag_in << 48;
+          int64_t spins = 0;
+          bool out = false;
+          for (;;) {
+            if (has) w = __hip_atomic_load(line + kw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (__all((uint32_t)(w >> 48) == tag_in)) break;
+            if ((out = give_up(++spins))) break;
+          }
+          if (out) break;
+          int cnt = (kw == 0 && has) ? (int)((w >> 32) & 0xffffu) : 0;
+          int incl = cnt;
+#pragma unroll
+          for (int d = 4; d < 64; d <<= 1) {
+            const int t = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += t;
+          }
+          const int tot = __shfl(incl, 60, 64);
+          const int pre = __shfl(incl - cnt, lane & ~3, 64);
+          cnt = __shfl(cnt, lane & ~3, 64);
+          if (c0 == 0) {
+            int w0 = 0;
+            if (lane == 0 && tot)
+              w0 = __hip_atomic_fetch_add(&s_tot, tot, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_WORKGROUP);
+            w0 = __builtin_amdgcn_readfirstlane(w0);
+            if (gi == 0) wbase[0] = w0;
+            else wbase[1] = w0;
+          }
+          const int base = (gi == 0 ? wbase[0] : wbase[1]) - (int)c0 + pre;
+          const int first = kw == 0 ? 0 : 3 * kw - 1;
+          put_word(w, blk, first, kw == 0 ? 2 : 3, cnt, base + first);
+          // the other words of lines with more spikes: two lines at a time,
+          // the next pair's words in flight
+          uint64_t more = __ballot(kw == 0 && cnt > kXchFirst);
+          if (more) {
+            const int half = lane >> 5, mw = kXchPoll + (lane & 31);
+            auto next_line = [&]() {
+              const int l0 = more ? (int)__builtin_ctzll(more) : 64;
+              more &= more - (more ? 1 : 0);
+              const int l1 = more ? (int)__builtin_ctzll(more) : 64;
+              more &= more - (more ? 1 : 0);
+              return half ? l1 : l0;
+            };
+            auto fetch = [&](int hl, bool need) {
+              return need ? __hip_atomic_load(xin + (size_t)(g + (hl >> 2)) * kXchWords + mw,
+                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                          : (uint64_t)tag_in << 48;
+            };
+            int hl = next_line();
+            int c = __shfl(cnt, hl & 63, 64);
+            if (hl == 64) c = 0;
+            bool need = hl < 64 && mw < kXchWords && 3 * mw - 1 < c;
+            uint64_t v = fetch(hl, need);
+            for (;;) {
+              const int hn = next_line();
+              const int cs = __shfl(cnt, hn & 63, 64), at = __shfl(base, hl & 63, 64);
+              const int cn = hn < 64 ? cs : 0;
+              const bool nn = hn < 64 && mw < kXchWords && 3 * mw - 1 < cn;
+              const uint64_t vn = fetch(hn, nn);
+              while (!__all((uint32_t)(v >> 48) == tag_in)) {
+                if ((out = give_up(++spins))) break;
+                v = fetch(hl, need);
+              }
+              if (out) break;
+              if (need) put_word(v, g + (hl >> 2), 3 * mw - 1, 3, c, at + 3 * mw - 1);
+              if (!__any(hn < 64)) break;
+              hl = hn;
+              c = cn;
+              need = nn;
+              v = vn;
+            }
+            if (out) break;
+          }
+          // spikes past a line's capacity: the block's part of the list buffer
+          if (__any(cnt > kXchMax)) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+#pragma unroll 1
+            for (int l = 0; l < 64; l += 4) {
+              const int c = __shfl(cnt, l, 64), at = __shfl(base, l, 64);
+              const uint32_t* from = ilist + (size_t)(g + (l >> 2)) * B * Dmin;
+              for (int i = kXchMax + lane; i < c; i += 64) {
+                if (at + i < 0 || at + i >= CAP) continue;
+                const uint32_t x =
+                    __hip_atomic_load(from + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                put(at + i, a.seg[(size_t)(x >> 5) * NB + b], x >> 5, (int)(x & 31u));
+              }
+            }
+          }
+        }
+      } else {
+        for (int64_t i = c0 + tid; i < total && i < c0 + CAP; i += kSliceThreads) {
+          const uint32_t ent = ilist[i];
           const uint32_t src = ent >> 5;
           const int lag = (int)(ent & 31u);
           uint2 sg = make_uint2(0u, 0u);
           if (lag < Dmin && (int64_t)src < a.n_src) sg = a.seg[(int64_t)src * NB + b];
           else atomicOr(a.overflow, 4);
-          desc[tid] = sg;
-          // ring offset of the spike's arrival rows: row (base + lag + delay
-          // - Dmin) mod R, the modulo taken per synapse
-          meta[tid] = ((uint32_t)((lag + base) * B) << 7) | (sg.y < 65u ? sg.y : 65u) |
-                      (((int64_t)src >= a.src_e_end) ? 0x80000000u : 0u);
-          ev += sg.y;
-        }
-        if (tid == 0) s_next = 0;
-        __syncthreads();
-        for (;;) {
-          int g0 = 0;
-          if (lane == 0)
-            g0 = __hip_atomic_fetch_add(&s_next, G, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          g0 = __builtin_amdgcn_readfirstlane(g0);
-          if (g0 >= n_c) break;
-          const int n_here = (n_c - g0) < G ? (n_c - g0) : G;
-          SynRaw<WF> raw[G];
-#pragma unroll
-          for (int u = 0; u < G; ++u) {
-            const uint2 d = desc[g0 + u];  // past the chunk: stale or padding, masked
-            const bool on = (u < n_here) & (lane < (int)d.y);
-            raw[u] = syn_fetch<WF>(a.syn, a.syn_dly, on ? d.x + (uint32_t)lane : 0u);
-          }
-          bool any_long = false;
-#pragma unroll
-          for (int u = 0; u < G; ++u) {
-            const uint32_t m = __builtin_amdgcn_readfirstlane(meta[g0 + u]);
-            any_long |= (u < n_here) & ((m & 127u) > 64u);
-            const bool inh = (int32_t)m < 0;
-            if ((u < n_here) & (lane < (int)(m & 127u)) & (lane < 64)) {
-              int slot, v;
-              syn_decode<WF>(raw[u], (int32_t)j0, Dmin, B, inh ? m0i : m0e, inh ? m1i : m1e,
-                             slot, v);
-              uint32_t x = ((m >> 7) & 0xffffffu) + (uint32_t)slot;
-              x = min(x, x - (uint32_t)RB);  // below 2 R B: one wrap at most
-              __hip_atomic_fetch_add((unsigned long long*)&win[x], (unsigned long long)(long long)v,
-                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-          }
-          // segments longer than one wave
-          if (any_long) {
-            for (int u = 0; u < n_here; ++u) {
-              const uint2 d = desc[g0 + u];
-              const uint32_t m = meta[g0 + u];
-              const int sl = __builtin_amdgcn_readfirstlane((int)d.y);
-              const bool inh = (int32_t)m < 0;
-              for (int e0 = 64; e0 < sl; e0 += 64) {
-                const bool on = lane + e0 < sl;
-                const SynRaw<WF> xr =
-                    syn_fetch<WF>(a.syn, a.syn_dly, on ? d.x + (uint32_t)(e0 + lane) : 0u);
-                if (on) {
-                  int slot, v;
-                  syn_decode<WF>(xr, (int32_t)j0, Dmin, B, inh ? m0i : m0e, inh ? m1i : m1e,
-                                 slot, v);
-                  uint32_t x = ((m >> 7) & 0xffffffu) + (uint32_t)slot;
-                  x = min(x, x - (uint32_t)RB);
-                  __hip_atomic_fetch_add((unsigned long long*)&win[x],
-                                         (unsigned long long)(long long)v, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_WORKGROUP);
-                }
-              }
-            }
-          }
+          put((int)(i - c0), sg, src, lag < Dmin ? lag : 0);
         }
       }
-#pragma unroll
-      for (int d = 32; d > 0; d >>= 1) ev += __shfl_xor(ev, d, 64);
-      if (lane == 0 && ev)
-        __hip_atomic_fetch_add(&s_ev, (unsigned long long)ev, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
-      if (b == 0 && tid == 0) in_all += (unsigned long long)total;
+      __syncthreads();  // descriptors; window rows cleared; LDS spike list read
+      if (tid == 0) s_cnt = 0;
+      if (k > 0) {
+        if (s_abort) {
+          ok = false;
+          break;
+        }
+        total = s_tot;
+      }
+      const int n_c = (int)(total - c0 < CAP ? total - c0 : CAP);
+      walk_chunk<WF>(a, desc, meta, n_c, &s_next, win, (int32_t)j0, Dmin, B, lane);
+      __syncthreads();  // window adds and drive counts complete
+      if (c0 + CAP >= total) break;
     }
-    __syncthreads();  // window adds and drive counts complete
-    // ---- update of the slice's Dmin steps, reading (and clearing) the ring
+    if (!ok) break;
+    if (tid == 0) {
+      s_tot = 0;
+      if (b == 0) in_all += (unsigned long long)total;
+    }
+    // ---- update of the slice's steps ---------------------------------------
+    const bool last = k + 1 == S;
     if (own) {
+      const float P11 = a.prop[0], P21 = a.prop[1], P22 = a.prop[2], P31 = a.prop[3];
+      const float P32 = a.prop[4], P33 = a.prop[5], P30Ie = a.prop[6], insc = a.prop[7];
+      const float drive_w = a.drive_w, e_l = a.e_l, v_th = a.v_th, v_reset = a.v_reset;
+      const int ref_steps = a.ref_steps;
+      const bool delta = a.model == MODEL_DELTA;
+      int dr = db, cr = cb, lr = lb;
+      auto read_row = [&](int s, long long& wq, uint32_t& dc, float& cv) {
+        wq = win[s * B + tid];
+        dc = dcnt[dr * B + tid];
+        cv = 0.f;
+        if (s < R) {
+          if constexpr (CL) cv = carry[cr * B + tid];
+          else cv = a.rb[(int64_t)lr * N + gn];
+        }
+        if (++dr == drows) dr = 0;
+        if (++cr >= R) cr = 0;
+        if (++lr == a.L) lr = 0;
+      };
+      uint32_t fired = 0;
+      long long wq;
+      uint32_t dc;
+      float cv;
+      read_row(0, wq, dc, cv);
+#pragma unroll 1
       for (int s = 0; s < Dmin; ++s) {
-        const int64_t t = w_lo + s;
-        long long* cell = &win[(int)(t % R) * B + tid];
-        float in = from_fixed(*cell, inv);
-        *cell = 0;
-        if (t < rb_hi0) in += a.rb[(t % a.L) * a.N + gn];  // sums from before the launch
-        const float drive = (float)dcnt[s * B + tid] * drive_w;
+        const float in = cv + from_fixed(wq, inv);
+        const float drv = (float)dc * drive_w;
+        win[s * B + tid] = 0;
+        if (s + 1 < Dmin) read_row(s + 1, wq, dc, cv);
         if (delta) {
-          if (rf > 0) --rf;
-          else V = e_l + P33 * (V - e_l) + P30Ie + in + drive;
+          const float Vn = e_l + P33 * (V - e_l) + P30Ie + in + drv;
+          V = rf > 0 ? V : Vn;
         } else {
-          if (rf == 0) V = e_l + P31 * y1 + P32 * y2 + P33 * (V - e_l) + P30Ie;
-          else --rf;
+          const float Vn = e_l + P31 * y1 + P32 * y2 + P33 * (V - e_l) + P30Ie;
+          V = rf > 0 ? V : Vn;
           const float y2n = P21 * y1 + P22 * y2;
-          y1 = P11 * y1 + insc * (in + drive);
+          y1 = P11 * y1 + insc * (in + drv);
           y2 = y2n;
         }
+        rf = rf > 0 ? rf - 1 : 0;
         const bool spk = V >= v_th;
-        if (spk) {
-          V = v_reset;
-          rf = ref_steps;
+        V = spk ? v_reset : V;
+        rf = spk ? ref_steps : rf;
+        fired |= (uint32_t)spk << s;
+      }
+      // ---- new spikes to the block's LDS list ------------------------------
+#pragma unroll 1
+      while (fired) {
+        const int s = __ffs(fired) - 1;
+        fired &= fired - 1;
+        const int at =
+            __hip_atomic_fetch_add(&s_cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (at < kPubCap) {
+          pub[at] = (uint16_t)(tid | (s << 10));
+          continue;
         }
-        const uint64_t bal = __ballot(spk);
-        if (lane == 0) {
-          const int w0 = (tid - lane) >> 5;
-          mask[s * Wd + w0] = (uint32_t)bal;
-          mask[s * Wd + w0 + 1] = (uint32_t)(bal >> 32);
+        const uint32_t ent = ((uint32_t)gn << 5) | (uint32_t)s;
+        if (!last) {  // past the LDS list: the block's part of the buffer
+          __hip_atomic_store(olist + (size_t)b * B * Dmin + at, ent, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+          const int64_t pos = atomicAdd(pp->cnt3 + (pp->ci0 + 1) % 3, 1);
+          if (pos < a.out_cap) olist[pos] = ent;
+          else atomicOr(a.overflow, 1);
+        }
+        if (a.rec) {
+          const unsigned long long rp = atomicAdd(a.rec_n, 1ull);
+          if ((int64_t)rp < a.rec_cap) a.rec[rp] = make_uint2((uint32_t)(w_lo + s), (uint32_t)gn);
+          else atomicOr(a.overflow, 2);
         }
       }
     }
-    __syncthreads();
-    // ---- compaction into slice k + 1's list, (lag, neuron) ordered -------
-    if (live) {
-      const int nq = Dmin * Wd;
-      for (int q0 = 0; q0 < nq; q0 += kSliceThreads) {
-        const int q = q0 + tid;
-        uint32_t m = (q < nq) ? mask[q] : 0u;
-        int tot;
-        const int ex = block_excl_scan<int>(__popc(m), scr, tot);
-        if (tot == 0) continue;
-        if (tid == 0) {
-          s_base = atomicAdd(out_cnt, tot);
-          s_rbase = a.rec ? atomicAdd(a.rec_n, (unsigned long long)tot) : 0ull;
-        }
+    __syncthreads();  // spike list complete
+    const int n_spk = s_cnt;
+    const int n_lds = n_spk < kPubCap ? n_spk : kPubCap;
+    auto list_entry = [&](int i) {
+      const uint32_t e = pub[i];
+      return ((uint32_t)(j0 + (e & 1023u)) << 5) | (e >> 10);
+    };
+    // ---- publish: the slice's line, or at the end the ordinary spike list --
+    if (!last) {
+      if (n_spk > kXchMax) {
+        for (int i = kXchMax + tid; i < n_lds; i += kSliceThreads)
+          __hip_atomic_store(olist + (size_t)b * B * Dmin + i, list_entry(i), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
-        const int64_t lbase = s_base;
-        const unsigned long long rbase = s_rbase;
-        __syncthreads();
-        int pos = ex;
-        const int lg = q / Wd;
-        const int nbase = (q % Wd) * 32;
-        while (m) {
-          const int bit = __ffs(m) - 1;
-          m &= m - 1;
-          const int64_t g = j0 + nbase + bit;
-          if (lbase + pos < a.out_cap) out_list[lbase + pos] = ((uint32_t)g << 5) | (uint32_t)lg;
-          else atomicOr(a.overflow, 1);
-          if (a.rec) {
-            const unsigned long long rp = rbase + (unsigned long long)pos;
-            if ((int64_t)rp < a.rec_cap) a.rec[rp] = make_uint2((uint32_t)(w_lo + lg), (uint32_t)g);
-            else atomicOr(a.overflow, 2);
-          }
-          ++pos;
-        }
-        if (tid == 0) spk_all += (unsigned long long)tot;
+        if (wv == 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       }
+      if (tid < kXchWords) {
+        const int first = tid == 0 ? 0 : 3 * tid - 1;
+        const int n = n_lds - first < (tid == 0 ? 2 : 3) ? n_lds - first : (tid == 0 ? 2 : 3);
+        // pub holds kPubCap > kXchMax + 3 entries: read first, masked after
+        uint64_t e0 = pub[first], e1 = pub[first + 1], e2 = pub[first + 2];
+        e0 = n > 0 ? e0 : 0;
+        e1 = n > 1 ? e1 : 0;
+        e2 = n > 2 ? e2 : 0;
+        if (tid == 0) e2 = (uint32_t)n_spk;
+        __hip_atomic_store(
+            pp->xch + ((size_t)(tag & 1u) * NB + b) * kXchWords + tid,
+            (uint64_t)tag << 48 | e2 << 32 | e1 << 16 | e0, __ATOMIC_RELAXED,
+            __HIP_MEMORY_SCOPE_AGENT);
+      }
+    } else if (n_lds > 0 && wv == 0) {
+      int base = 0;
+      if (lane == 0) base = atomicAdd(pp->cnt3 + (pp->ci0 + 1) % 3, n_lds);
+      base = __builtin_amdgcn_readfirstlane(base);
+      for (int i = lane; i < n_lds; i += 64) {
+        if ((int64_t)base + i < a.out_cap) olist[base + i] = list_entry(i);
+        else atomicOr(a.overflow, 1);
+      }
+    }
+    if (a.rec && n_lds > 0 && wv == nwv - 1) {
+      unsigned long long rb0 = 0;
+      if (lane == 0) rb0 = atomicAdd(a.rec_n, (unsigned long long)n_lds);
+      rb0 = __shfl(rb0, 0, 64);
+      for (int i = lane; i < n_lds; i += 64) {
+        const uint32_t e = pub[i];
+        const unsigned long long rp = rb0 + (unsigned long long)i;
+        if ((int64_t)rp < a.rec_cap)
+          a.rec[rp] = make_uint2((uint32_t)(w_lo + (e >> 10)), (uint32_t)(j0 + (e & 1023u)));
+        else atomicOr(a.overflow, 2);
+      }
+    }
+    if (tid == 0) spk_all += (unsigned long long)n_spk;
+    // ---- rows due later: rounded once and added to the carried sums -------
+    if (own) {
+      int row = cb + Dmin, lr = lb + Dmin;
+      while (R > 0 && row >= R) row -= R;
+      if (lr >= a.L) lr -= a.L;
+#pragma unroll 1
+      for (int q0 = Dmin; q0 < Dmax; q0 += 4) {
+        // four rows' reads, then their stores
+        long long wq[4];
+        float old[4];
+        float* cell[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int q = q0 + i < Dmax ? q0 + i : Dmax - 1;
+          wq[i] = win[q * B + tid];
+          cell[i] = CL ? carry + row * B + tid : a.rb + (int64_t)lr * N + gn;
+          old[i] = q < R ? *cell[i] : 0.f;
+          if (q0 + i + 1 < Dmax) {
+            if (++row == R) row = 0;
+            if (++lr == a.L) lr = 0;
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (q0 + i >= Dmax) break;
+          win[(q0 + i) * B + tid] = 0;
+          *cell[i] = old[i] + from_fixed(wq[i], inv);
+        }
+      }
+    }
+    if (R > 0) {
+      cb += Dmin;
+      while (cb >= R) cb -= R;
+    }
+    lb += Dmin;
+    if (lb >= a.L) lb -= a.L;
+    if (dring) {
+      db += Dmin;
+      while (db >= drows) db -= drows;
     }
     cur ^= 1;
-    ci = (ci + 1) % 3;
-    if (k + 1 < S)
-      ok = grid_barrier(pp->bar, (unsigned)gridDim.x * (unsigned)(k + 1), a.overflow,
-                        pp->spin_limit);
   }
-  if (!live) return;
-  // ---- rows due after the last slice go to the HBM ring ---------------------
-  const int64_t t_end = t0 + (int64_t)S * Dmin;
-  const bool delivered = S > 1 || pp->pend0;
-  if (ok && delivered && own) {
-    const int64_t hi = t_end - Dmin + R;  // end of the last delivery window
-    for (int64_t t = t_end; t < hi; ++t) {
-      const float v = from_fixed(win[(int)(t % R) * B + tid], inv);
-      float* cell = a.rb + (t % a.L) * a.N + gn;
-      *cell = (t < rb_hi0) ? *cell + v : v;
-    }
-  }
+  // ---- sums of the rows not yet due go to the HBM ring ---------------------
   if (own) {
+    if constexpr (CL) {
+      if (ok)
+        for (int q = 0; q < R; ++q) {
+          int row = cb + q, lr = lb + q;
+          if (row >= R) row -= R;
+          if (lr >= a.L) lr -= a.L;
+          a.rb[(int64_t)lr * N + gn] = carry[row * B + tid];
+        }
+    }
     a.V[gn] = V;
     a.r[gn] = rf;
     if (a.model == MODEL_ALPHA) {
@@ -2114,7 +2456,11 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
       a.y2[gn] = y2;
     }
   }
-  __syncthreads();  // s_ev complete
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) ev += __shfl_xor(ev, d, 64);
+  if (lane == 0 && ev)
+    __hip_atomic_fetch_add(&s_ev, ev, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  __syncthreads();
   if (tid == 0) {
     if (s_ev) atomicAdd(a.ev_count, s_ev);
     if (in_all) atomicAdd(a.spk_in_count, in_all);
@@ -2133,10 +2479,6 @@ __global__ void k_zero_rows(float* rb, int64_t N, int32_t L, int64_t t_lo, int64
     rb[(t % L) * N + (i % N)] = 0.f;
   }
 }
-
-// One word set by a one-thread kernel: a clear issued on a stream that a
-// caller may be capturing becomes a kernel node rather than a memset node.
-__global__ void k_set_word(unsigned* p, unsigned v) { *p = v; }
 
 // An external spike list (separate source and lag arrays) packed into the
 // delivery's entry format (src << 5 | lag), validated on the device: an
@@ -2359,25 +2701,30 @@ hipError_t launch_slice1(hipStream_t s, const SliceArgs& a, size_t lds, int wfor
   return hipGetLastError();
 }
 
-// Workgroups per CU that a persistent launch of this weight form can hold.
-int persist_occupancy(int wform, size_t lds) {
-  int occ = 0;
-  hipError_t e;
+// The kernel of a weight form and carry placement.
+const void* persist_kernel(int wform, bool cl) {
   switch (wform) {
-    case WF_FP32: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_persist<WF_FP32>, kSliceThreads, lds); break;
-    case WF_BF16: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_persist<WF_BF16>, kSliceThreads, lds); break;
-    case WF_PACKED: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_persist<WF_PACKED>, kSliceThreads, lds); break;
-    default: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_persist<WF_BF16_RESID>, kSliceThreads, lds); break;
+    case WF_FP32: return cl ? (const void*)k_persist<WF_FP32, true> : (const void*)k_persist<WF_FP32, false>;
+    case WF_BF16: return cl ? (const void*)k_persist<WF_BF16, true> : (const void*)k_persist<WF_BF16, false>;
+    case WF_PACKED: return cl ? (const void*)k_persist<WF_PACKED, true> : (const void*)k_persist<WF_PACKED, false>;
+    default: return cl ? (const void*)k_persist<WF_BF16_RESID, true> : (const void*)k_persist<WF_BF16_RESID, false>;
   }
+}
+
+// Workgroups per CU that a persistent launch of this weight form can hold.
+int persist_occupancy(int wform, const PersistPlan& plan) {
+  int occ = 0;
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+      &occ, persist_kernel(wform, plan.carry_lds), kSliceThreads, plan.lds);
   return e == hipSuccess ? occ : 0;
 }
 
 // Cooperative launch: the runtime refuses a grid that cannot be resident at
-// once, so the grid barriers cannot wait on a workgroup that never starts.
+// once, so no workgroup waits for the line of one that never starts.
 hipError_t launch_persist(hipStream_t s, const SliceArgs& a, uint32_t* const lists[2],
                           int32_t* cnt3, int32_t cur0, int32_t ci0, int32_t pend0, int32_t S,
-                          int64_t t0, int64_t rb_hi0, unsigned* bar, int64_t spin_limit,
-                          size_t lds, int wform) {
+                          int64_t t0, int64_t rb_hi0, void* xch, uint32_t epoch0,
+                          int64_t spin_limit, const PersistPlan& plan, int wform) {
   PersistArgs p;
   p.a = a;
   p.lists[0] = lists[0];
@@ -2388,18 +2735,17 @@ hipError_t launch_persist(hipStream_t s, const SliceArgs& a, uint32_t* const lis
   p.pend0 = pend0;
   p.S = S;
   p.per_xcd = (a.NB + 7) / 8;
+  p.cap = plan.cap;
+  p.drows = plan.drows;
+  p.epoch0 = epoch0;
   p.t0 = t0;
   p.rb_hi0 = rb_hi0;
-  p.bar = bar;
+  p.xch = (uint64_t*)xch;
   p.spin_limit = spin_limit < 0 ? kBarSpin : spin_limit;
   void* args[] = {&p};
   const dim3 grid((unsigned)(8 * p.per_xcd)), block(kSliceThreads);
-  switch (wform) {
-    case WF_FP32: return hipLaunchCooperativeKernel((const void*)k_persist<WF_FP32>, grid, block, args, lds, s);
-    case WF_BF16: return hipLaunchCooperativeKernel((const void*)k_persist<WF_BF16>, grid, block, args, lds, s);
-    case WF_PACKED: return hipLaunchCooperativeKernel((const void*)k_persist<WF_PACKED>, grid, block, args, lds, s);
-    default: return hipLaunchCooperativeKernel((const void*)k_persist<WF_BF16_RESID>, grid, block, args, lds, s);
-  }
+  return hipLaunchCooperativeKernel(persist_kernel(wform, plan.carry_lds), grid, block, args,
+                                    plan.lds, s);
 }
 
 // Captured batches: the argument sets of a period of slices move on by
@@ -2415,11 +2761,6 @@ __global__ void k_shift_args(SliceArgs* args, int32_t n, int64_t shift) {
 
 hipError_t launch_shift_args(hipStream_t s, SliceArgs* args, int32_t n, int64_t shift) {
   hipLaunchKernelGGL(k_shift_args, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, s, args, n, shift);
-  return hipGetLastError();
-}
-
-hipError_t launch_set_word(hipStream_t s, unsigned* p, unsigned v) {
-  hipLaunchKernelGGL(k_set_word, dim3(1), dim3(1), 0, s, p, v);
   return hipGetLastError();
 }
 

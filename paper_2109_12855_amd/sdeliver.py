@@ -310,12 +310,14 @@ class Net:
 
     def set_persistent(self, max_slices: int):
         """Run up to max_slices whole slices per persistent launch (0: one
-        launch per slice)."""
+        launch per slice; a new net runs stretches of 4 and more slices
+        persistently where it can)."""
         self._check(lib().sd_set_persistent(self._h, int(max_slices)), "sd_set_persistent")
 
     def set_barrier_spin(self, polls: int):
-        """Polls a persistent launch's grid barrier waits before it gives up
-        (overflow bit 16); < 0 restores the default."""
+        """Polls a workgroup of a persistent launch waits for the others'
+        spikes before it gives up (overflow bit 16); < 0 restores the
+        default."""
         self._check(lib().sd_set_barrier_spin(self._h, int(polls)), "sd_set_barrier_spin")
 
     # -- read-back --------------------------------------------------------------
