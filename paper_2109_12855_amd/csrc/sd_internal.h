@@ -122,6 +122,7 @@ struct BuildArgs {
   uint32_t* row;           // (src, block) counts, then exclusive scan (block-major)
   uint32_t* cursor;        // fill cursors (copy of row)
   uint2* seg;              // source-major (start, count) pairs
+  uint64_t* xch;           // exchange lines of persistent slices to clear (null: none)
   // source-major layout: one segment per (source, target part), parts of
   // 2^tbits targets; record word = offset in part | (delay - d_min) << tbits
   // | weight bits 8-15 << 24 (BF16 forms), plus the weight's low byte (u8) or

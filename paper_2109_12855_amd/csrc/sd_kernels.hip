@@ -350,8 +350,11 @@ __global__ void __launch_bounds__(kFillThreads) k_fill(BuildArgs a) {
 
 // Segment pointers: seg[s * NB + b] = (start, count) of the synapses from s
 // into block b, from the scan of the (s, b) counts.
-__global__ void k_seg_pairs(const uint32_t* row, int64_t n_src, int32_t NB, uint2* seg) {
+// Clears the n_xch words of the persistent slices' exchange lines on the way.
+__global__ void k_seg_pairs(const uint32_t* row, int64_t n_src, int32_t NB, uint2* seg,
+                            uint64_t* xch, int32_t n_xch) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t x = i; x < n_xch; x += (int64_t)gridDim.x * blockDim.x) xch[x] = 0;
   if (i >= n_src * NB) return;
   const uint32_t lo = row[i];
   seg[i] = make_uint2(lo, row[i + 1] - lo);
@@ -2637,7 +2640,7 @@ hipError_t launch_gather_block(hipStream_t s, const uint2* seg, int64_t n_src, i
 hipError_t launch_seg_pairs(hipStream_t s, const BuildArgs& a) {
   const int64_t n = a.n_src * a.NB;
   hipLaunchKernelGGL(k_seg_pairs, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.row, a.n_src,
-                     a.NB, a.seg);
+                     a.NB, a.seg, a.xch, a.xch ? (int32_t)(xch_bytes(a.NB) / 8) : 0);
   return hipGetLastError();
 }
 

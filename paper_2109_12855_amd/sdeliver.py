@@ -335,14 +335,14 @@ class Net:
 
     def ring(self, n_slots: int | None = None) -> np.ndarray:
         n_slots = self.ring_len if n_slots is None else n_slots
-        out = np.zeros((n_slots, self.n_local), np.float32)
+        out = np.empty((n_slots, self.n_local), np.float32)
         self._check(lib().sd_read_ring(self._h, _ptr(out), int(n_slots)), "sd_read_ring")
         return out
 
     def state(self) -> dict:
         n = self.n_local
-        v, y1, y2 = (np.zeros(n, np.float32) for _ in range(3))
-        r = np.zeros(n, np.int32)
+        v, y1, y2 = (np.empty(n, np.float32) for _ in range(3))
+        r = np.empty(n, np.int32)
         self._check(lib().sd_read_state(self._h, _ptr(v), _ptr(y1), _ptr(y2), _ptr(r)),
                     "sd_read_state")
         return {"V": v, "y1": y1, "y2": y2, "r": r}
