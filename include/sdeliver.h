@@ -51,16 +51,18 @@ typedef enum {
 
 typedef enum { SD_IAF_PSC_DELTA = 0, SD_IAF_PSC_ALPHA = 1 } sd_model;
 
-/* Storage form of a synapse (weight, target, delay):
- *   SD_W_FP32        f32 weight, i32 target id, u8 delay       (9 B / synapse)
- *   SD_W_BF16        bf16 weight, u16 offset in block, u8 delay (5 B)
+/* Storage form of a synapse (weight, target, delay); the slot is its place in
+ * the target block's ring window, (delay - d_min) * block_neurons + offset in
+ * block:
+ *   SD_W_FP32        f32 weight, u16 slot and u8 delay - d_min in one 32-bit
+ *                    word, u8 delay (exports)                   (9 B / synapse)
+ *   SD_W_BF16        bf16 weight, u16 slot, u8 delay (exports)  (5 B)
  *   SD_W_BF16_RESID  bf16 residual d, w = mu_pop * (1 + d), where mu_pop is
  *                    the FP32 mean weight of the source's population,
- *                    u16 offset in block, u8 delay              (5 B)
- *   SD_W_BF16_PACKED the residual weight (low half) and the ring-window slot
- *                    (delay - d_min) * block_neurons + offset in block
- *                    (high half) in one 32-bit word             (4 B);
+ *                    u16 slot, u8 delay (exports)               (5 B)
+ *   SD_W_BF16_PACKED the residual weight and the slot           (4 B);
  *                    needs (d_max - d_min + 1) * block_neurons <= 65536
+ * A delivery reads 8 bytes per event in the FP32 form and 4 in the others.
  * In the source-major layout the targets are cut into parts of 2^tbits
  * (tbits = 24 - the bits of d_max - d_min, at most 4 parts) and each source
  * has one segment per part.  A record is a u32 {offset in the part (tbits),

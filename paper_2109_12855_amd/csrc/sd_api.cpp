@@ -766,7 +766,6 @@ SliceArgs base_args(sd_ctx* c) {
   a.seg = c->seg;
   a.n_src = c->n_src;
   a.syn = c->syn;
-  a.syn_dly = c->syn_dly;
   a.K = c->K;
   a.N = c->N;
   a.NB = c->NB;
@@ -895,29 +894,25 @@ sd_status bin_events(sd_ctx* c, const uint32_t* in_list, const int32_t* in_cnt, 
 // Decode record e of a host copy of the synapse arrays (b: its block).
 void decode_record(const sd_config& g, const uint8_t* rec, const uint8_t* dl, uint32_t e,
                    int32_t b, int32_t B, float mu, int32_t* tgt, float* w, uint8_t* dly) {
+  uint32_t slot;
   if (g.wform == SD_W_FP32) {
     uint64_t r;
     std::memcpy(&r, rec + (size_t)e * 8, 8);
     const uint32_t wb = (uint32_t)r;
     std::memcpy(w, &wb, 4);
-    *tgt = (int32_t)(r >> 32);
-    *dly = dl[e];
-    return;
-  }
-  uint32_t r;
-  std::memcpy(&r, rec + (size_t)e * 4, 4);
-  const uint32_t u = r << 16;
-  float d;
-  std::memcpy(&d, &u, 4);
-  *w = g.wform == SD_W_BF16 ? d : std::fma(mu, d, mu);
-  if (g.wform == SD_W_BF16_PACKED) {
-    const uint32_t slot = r >> 16;  // (delay - d_min) * B + offset
-    *tgt = (int32_t)((int64_t)b * B + (int32_t)(slot % (uint32_t)B));
-    *dly = (uint8_t)(g.d_min + (int)(slot / (uint32_t)B));
+    slot = (uint32_t)(r >> 32) & ((1u << kSynSlotBits) - 1u);
   } else {
-    *tgt = (int32_t)((int64_t)b * B + (r >> 16));
-    *dly = dl[e];
+    uint32_t r;
+    std::memcpy(&r, rec + (size_t)e * 4, 4);
+    const uint32_t u = r << 16;
+    float d;
+    std::memcpy(&d, &u, 4);
+    *w = g.wform == SD_W_BF16 ? d : std::fma(mu, d, mu);
+    slot = r >> kSynSlotBits;
   }
+  // slot = (delay - d_min) * B + offset
+  *tgt = (int32_t)((int64_t)b * B + (int32_t)(slot % (uint32_t)B));
+  *dly = g.wform == SD_W_BF16_PACKED ? (uint8_t)(g.d_min + (int)(slot / (uint32_t)B)) : dl[e];
 }
 
 // Point the delivery arguments at the completed slice's spikes: the

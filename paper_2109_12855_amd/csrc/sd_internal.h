@@ -19,14 +19,20 @@ constexpr int kSliceThreads = 1024;  // threads of a slice workgroup
 constexpr int kFillThreads = 512;    // threads of a build workgroup
 constexpr int kFillChunk = 2048;     // draws ranked per build iteration
 
-// Synapse record layouts (one record per synapse, plus a u8 delay array for
-// the first three forms):
-//   WF_FP32        u64: low word FP32 weight bits, high word i32 target id
-//   WF_BF16        u32: low half BF16 weight, high half u16 offset in block
+// Synapse record layouts of the block-major table.  Every record holds the
+// slot its weight goes to in the block's ring window, (delay - d_min) * B +
+// offset in block for a spike of lag 0: below d_max * B <= 20480, since the
+// window fits the LDS.
+//   WF_FP32        u64: low word FP32 weight bits, high word the slot (bits
+//                  0-15) and delay - d_min (bits 16-23, read by plastic nets)
+//   WF_BF16        u32: low half BF16 weight, high half the slot
 //   WF_BF16_RESID  u32: low half BF16 residual d (w = mu (1 + d)), high half
-//                  u16 offset in block
-//   WF_PACKED      u32: low half BF16 residual, high half the ring-window
-//                  slot (delay - d_min) * B + offset in block (no delay array)
+//   and WF_PACKED  the slot
+// All forms but the packed one also keep a u8 delay array (exports).
+constexpr int kSynSlotBits = 16;
+// kernel forms: records of 8 bytes, or of 4 (the BF16 forms differ in their
+// fixed-point constants only)
+enum { KF_F32 = 0, KF_16 = 1 };
 
 // Everything a slice launch needs (passed by value).
 struct SliceArgs {
@@ -34,7 +40,6 @@ struct SliceArgs {
   const uint2* seg;        // [n_src][NB]: (first synapse, count) of source s in block b
   int64_t n_src;           // source ids
   const void* syn;         // synapse records (layout per weight form)
-  const uint8_t* syn_dly;  // u8 delay in steps (not used by the packed form)
   int64_t N;               // local neurons
   int32_t NB, B;           // blocks, neurons per block
   int32_t K;               // in-degree: block b's synapses start at b * B * K

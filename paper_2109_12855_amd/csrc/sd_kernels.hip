@@ -317,20 +317,19 @@ __global__ void __launch_bounds__(kFillThreads) k_fill(BuildArgs a) {
       const uint32_t m = meta[idx];
       const uint32_t widx = m & 0xffffu, inh = (m >> 16) & 1u, dly = m >> 24;
       const int64_t jl = (c0 + idx) / a.K;
+      const uint32_t slot = (dly - (uint32_t)a.d_min) * (uint32_t)a.B + (uint32_t)jl;
       if (a.wform == WF_FP32) {
         float w;
         if (a.fixed) w = inh ? a.w_fix_i : a.w_fix_e;
         else w = inh ? ((const float*)a.wtab_i)[widx] : ((const float*)a.wtab_e)[widx];
         ((uint64_t*)a.syn)[pos] =
-            ((uint64_t)(uint32_t)(j0 + jl) << 32) | (uint64_t)__float_as_uint(w);
+            ((uint64_t)(slot | ((dly - (uint32_t)a.d_min) << kSynSlotBits)) << 32) |
+            (uint64_t)__float_as_uint(w);
       } else {
         uint32_t wb;
         if (a.fixed) wb = inh ? a.fix_bits_i : a.fix_bits_e;
         else wb = inh ? ((const uint16_t*)a.wtab_i)[widx] : ((const uint16_t*)a.wtab_e)[widx];
-        uint32_t rec = (wb & 0xffffu) | ((uint32_t)jl << 16);
-        if (a.wform == WF_PACKED)
-          rec = (wb & 0xffffu) | ((uint32_t)((int64_t)(dly - a.d_min) * a.B + jl) << 16);
-        ((uint32_t*)a.syn)[pos] = rec;
+        ((uint32_t*)a.syn)[pos] = (wb & 0xffffu) | (slot << kSynSlotBits);
       }
       if (a.wform != WF_PACKED) a.syn_dly[pos] = (uint8_t)dly;
     }
@@ -807,20 +806,18 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(BinArgs args) {
 // ---------------------------------------------------------------------------
 // Raw synapse record as loaded (decoded only when its add is issued, so a
 // wave keeps one to three registers per segment in flight).
-template <int WF> struct SynRaw;
-template <> struct SynRaw<WF_FP32> { uint64_t r; uint32_t d; };
-template <> struct SynRaw<WF_BF16> { uint32_t r; uint32_t d; };
-template <> struct SynRaw<WF_BF16_RESID> { uint32_t r; uint32_t d; };
-template <> struct SynRaw<WF_PACKED> { uint32_t r; };
+// KF: KF_F32 (8-byte records, plastic nets too) or KF_16 (4-byte records).
+template <int KF> struct SynRaw;
+template <> struct SynRaw<KF_F32> { uint2 r; };
+template <> struct SynRaw<KF_16> { uint32_t r; };
 
 // Segments a wave takes from the chunk at a time (all loads in flight
 // before the adds).  Measured on the 112,500-neuron network (~44-synapse
 // segments): smaller groups spread a chunk's ~900 spikes more evenly over
 // the 16 waves and keep the blocks of an XCD on nearby spikes; below these
 // sizes the loads in flight no longer cover the latency.
-template <int WF> struct SynGroup { static constexpr int n = 12; };
-template <> struct SynGroup<WF_FP32> { static constexpr int n = 8; };
-template <> struct SynGroup<WF_PACKED> { static constexpr int n = 12; };
+template <int KF> struct SynGroup { static constexpr int n = 12; };
+template <> struct SynGroup<KF_F32> { static constexpr int n = 8; };
 constexpr int kMaxGroup = 32;
 
 // Binned records (source-major layout) are read through a buffer resource
@@ -832,20 +829,15 @@ constexpr int kBufWord3 = 0x00020000;  // gfx9 buffer resource: 32-bit dword for
 
 // Record i of the block-major table (index 0 for a lane or slot with
 // nothing to load: the table always holds a record there, the value is
-// not used).
-template <int WF>
-__device__ __forceinline__ SynRaw<WF> syn_fetch(const void* syn, const uint8_t* dly, uint32_t i) {
-  SynRaw<WF> x;
-  if constexpr (WF == WF_FP32) {
-    const uint2 v = ((const uint2*)syn)[i];
-    x.r = ((uint64_t)v.y << 32) | v.x;
-    x.d = dly[i];
-  } else if constexpr (WF == WF_PACKED) {
-    x.r = ((const uint32_t*)syn)[i];
-  } else {
-    x.r = ((const uint32_t*)syn)[i];
-    x.d = dly[i];
-  }
+// not used).  The u8 delay array is for exports: every record holds its
+// window slot, and a walk that also read a delay per synapse touched one to
+// two more lines of every segment (9 and 5 bytes per event instead of 8 and
+// 4).
+template <int KF>
+__device__ __forceinline__ SynRaw<KF> syn_fetch(const void* syn, uint32_t i) {
+  SynRaw<KF> x;
+  if constexpr (KF == KF_F32) x.r = ((const uint2*)syn)[i];
+  else x.r = ((const uint32_t*)syn)[i];
   return x;
 }
 
@@ -854,19 +846,16 @@ __device__ __forceinline__ SynRaw<WF> syn_fetch(const void* syn, const uint8_t* 
 // the window quantum chosen so that max|w| * 2^s <= 2^30, w * 2^s is exact
 // in FP32 for |w| * 2^s >= 2^23, so the truncation only rounds weights
 // below 2^-7 of the largest.
-template <int WF>
-__device__ __forceinline__ void syn_decode(const SynRaw<WF>& x, int32_t j0, int Dmin, int B,
-                                           float m0, float m1, int& slot, int& v) {
+template <int KF>
+__device__ __forceinline__ void syn_decode(const SynRaw<KF>& x, float m0, float m1, int& slot,
+                                           int& v) {
   float w;
-  if constexpr (WF == WF_FP32) {
-    w = __uint_as_float((uint32_t)x.r);
-    slot = ((int)x.d - Dmin) * B + ((int)(x.r >> 32) - j0);
-  } else if constexpr (WF == WF_PACKED) {
-    w = __uint_as_float(x.r << 16);
-    slot = (int)(x.r >> 16);
+  if constexpr (KF == KF_F32) {
+    w = __uint_as_float(x.r.x);
+    slot = (int)(x.r.y & ((1u << kSynSlotBits) - 1u));
   } else {
     w = __uint_as_float(x.r << 16);
-    slot = ((int)x.d - Dmin) * B + (int)(x.r >> 16);
+    slot = (int)(x.r >> kSynSlotBits);
   }
   v = (int)fmaf(m1, w, m0);  // conversion truncates toward zero
 }
@@ -995,11 +984,12 @@ __device__ __forceinline__ float plastic_walk(const SliceArgs& a, float w, int d
 // synapse's fixed-point weight into the ring window.  G loads issue back to
 // back (lanes past a segment's end and slots past the chunk read record 0,
 // unused), then the adds; the group bound is uniform.
-template <int WF>
+// in_flight() runs after each group's loads: work that needs none of them.
+template <int KF, typename F>
 __device__ __forceinline__ void walk_chunk(const SliceArgs& a, const uint2* desc,
                                            const uint32_t* meta, int n_c, int* s_next,
-                                           long long* win, int32_t j0, int Dmin, int B, int lane) {
-  constexpr int G = SynGroup<WF>::n;
+                                           long long* win, int lane, F in_flight) {
+  constexpr int G = SynGroup<KF>::n;
   for (;;) {
     int g0 = 0;
     if (lane == 0)
@@ -1007,13 +997,14 @@ __device__ __forceinline__ void walk_chunk(const SliceArgs& a, const uint2* desc
     g0 = __builtin_amdgcn_readfirstlane(g0);
     if (g0 >= n_c) break;
     const int n_here = (n_c - g0) < G ? (n_c - g0) : G;
-    SynRaw<WF> raw[G];
+    SynRaw<KF> raw[G];
 #pragma unroll
     for (int u = 0; u < G; ++u) {
       const uint2 d = desc[g0 + u];  // past the chunk: stale or padding, masked
       const bool on = (u < n_here) & (lane < (int)d.y) & (d.x != 0xffffffffu);
-      raw[u] = syn_fetch<WF>(a.syn, a.syn_dly, on ? d.x + (uint32_t)lane : 0u);
+      raw[u] = syn_fetch<KF>(a.syn, on ? d.x + (uint32_t)lane : 0u);
     }
+    in_flight();
     uint32_t mt[G];
     bool any_long = false;
 #pragma unroll
@@ -1032,7 +1023,7 @@ __device__ __forceinline__ void walk_chunk(const SliceArgs& a, const uint2* desc
       long long* row = win + ((m >> 7) & 0xffffffu);
       if ((u < n_here) & (lane < (int)(m & 127u))) {
         int slot, v;
-        syn_decode<WF>(raw[u], j0, Dmin, B, m0, m1, slot, v);
+        syn_decode<KF>(raw[u], m0, m1, slot, v);
         __hip_atomic_fetch_add((unsigned long long*)&row[slot], (unsigned long long)(long long)v,
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
@@ -1046,12 +1037,10 @@ __device__ __forceinline__ void walk_chunk(const SliceArgs& a, const uint2* desc
         const bool inh = (int)m < 0;
         for (int e0 = 64; e0 < sl; e0 += 64) {
           const bool on = lane + e0 < sl;
-          const SynRaw<WF> x =
-              syn_fetch<WF>(a.syn, a.syn_dly, on ? d.x + (uint32_t)(e0 + lane) : 0u);
+          const SynRaw<KF> x = syn_fetch<KF>(a.syn, on ? d.x + (uint32_t)(e0 + lane) : 0u);
           if (on) {
             int slot, v;
-            syn_decode<WF>(x, j0, Dmin, B, inh ? a.wm0_i : a.wm0_e, inh ? a.wm1_i : a.wm1_e,
-                           slot, v);
+            syn_decode<KF>(x, inh ? a.wm0_i : a.wm0_e, inh ? a.wm1_i : a.wm1_e, slot, v);
             __hip_atomic_fetch_add((unsigned long long*)&win[(int)((m >> 7) & 0xffffffu) + slot],
                                    (unsigned long long)(long long)v, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1062,12 +1051,95 @@ __device__ __forceinline__ void walk_chunk(const SliceArgs& a, const uint2* desc
   }
 }
 
+// The same walk for a plastic net: each lane's synapse takes the entry's
+// spikes in lag order (static inhibitory ones only add), its weight updated
+// before each add and stored back.
+__device__ __forceinline__ void plastic_synapse(const SliceArgs& a, uint2 r, uint32_t at, bool inh,
+                                                uint32_t lm, int32_t tprev, const uint64_t* pm,
+                                                const int32_t* pb, long long* win, int64_t w_lo,
+                                                int Dmin, int B) {
+  float w = __uint_as_float(r.x);
+  const int slot = (int)(r.y & ((1u << kSynSlotBits) - 1u));
+  if (inh) {
+    const int v = (int)(a.wm1_i * w);
+    while (lm) {
+      const int l = __ffs(lm) - 1;
+      lm &= lm - 1;
+      __hip_atomic_fetch_add((unsigned long long*)&win[l * B + slot],
+                             (unsigned long long)(long long)v, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  } else {
+    const int q = (int)(r.y >> kSynSlotBits), jl = slot - q * B;
+    w = plastic_walk(a, w, Dmin + q, pm[jl], pb[jl], lm, tprev, (int32_t)(w_lo - Dmin),
+                     (int32_t)w_lo, Dmin, B, jl, win, a.wm1_e);
+    ((uint32_t*)a.syn)[2 * (size_t)at] = __float_as_uint(w);
+  }
+}
+
+template <typename F>
+__device__ __forceinline__ void walk_plastic(const SliceArgs& a, const uint2* desc,
+                                             const uint32_t* meta, const uint32_t* lagm,
+                                             const int32_t* tpv, const uint64_t* pm,
+                                             const int32_t* pb, int n_c, int* s_next,
+                                             long long* win, int64_t w_lo, int Dmin, int B,
+                                             int lane, F in_flight) {
+  constexpr int G = SynGroup<KF_F32>::n;
+  for (;;) {
+    int g0 = 0;
+    if (lane == 0)
+      g0 = __hip_atomic_fetch_add(s_next, G, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    g0 = __builtin_amdgcn_readfirstlane(g0);
+    if (g0 >= n_c) break;
+    const int n_here = (n_c - g0) < G ? (n_c - g0) : G;
+    SynRaw<KF_F32> raw[G];
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const uint2 d = desc[g0 + u];  // past the chunk: stale or padding, masked
+      const bool on = (u < n_here) & (lane < (int)d.y) & (d.x != 0xffffffffu);
+      raw[u] = syn_fetch<KF_F32>(a.syn, on ? d.x + (uint32_t)lane : 0u);
+    }
+    in_flight();
+    uint32_t mt[G];
+    bool any_long = false;
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      mt[u] = meta[g0 + u];
+      any_long |= (mt[u] & 127u) > 64u;
+    }
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const uint32_t m = __builtin_amdgcn_readfirstlane(mt[u]);
+      const uint32_t lm = __builtin_amdgcn_readfirstlane(lagm[g0 + u]);
+      const int32_t tp0 = __builtin_amdgcn_readfirstlane(tpv[g0 + u]);
+      const uint32_t sx = __builtin_amdgcn_readfirstlane(desc[g0 + u].x);
+      if ((u < n_here) & (lane < (int)(m & 127u)) & (lane < 64))
+        plastic_synapse(a, raw[u].r, sx + (uint32_t)lane, (int32_t)m < 0, lm, tp0, pm, pb, win,
+                        w_lo, Dmin, B);
+    }
+    // segments longer than one wave
+    if (__builtin_amdgcn_readfirstlane((int)any_long)) {
+      for (int u = 0; u < n_here; ++u) {
+        const uint2 d = desc[g0 + u];
+        const uint32_t m = meta[g0 + u];
+        const int sl = __builtin_amdgcn_readfirstlane((int)d.y);
+        for (int e0 = 64; e0 < sl; e0 += 64) {
+          if (lane + e0 >= sl) continue;
+          const uint32_t at = d.x + (uint32_t)(e0 + lane);
+          plastic_synapse(a, syn_fetch<KF_F32>(a.syn, at).r, at, (int32_t)m < 0, lagm[g0 + u],
+                          tpv[g0 + u], pm, pb, win, w_lo, Dmin, B);
+        }
+      }
+    }
+  }
+}
+
 // One workgroup's slice for target block b of the network described by a.
 // BIN: the slice's events arrive binned by target block (source-major
-// layout, k_bin; WF_FP32 for 8-byte records, any other form for 4-byte
-// ones); otherwise they are read from the block-major segments.
+// layout, k_bin; 8- or 4-byte records); otherwise they are read from the
+// block-major segments.
 // DYN: how the window rows due later are flushed (see the flush below).
-template <int WF, bool BIN, bool DYN, bool PL = false>
+template <int KF, bool BIN, bool DYN, bool PL = false>
 __device__ __forceinline__ void slice_block(const SliceArgs& a, const int b) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int tid = threadIdx.x;
@@ -1229,7 +1301,7 @@ __device__ __forceinline__ void slice_block(const SliceArgs& a, const int b) {
     // past a region's count load nothing: their buffer offset is out of
     // range).  The record holds the window slot, so the adds need no
     // per-item state.
-    constexpr bool W8 = WF == WF_FP32;
+    constexpr bool W8 = KF == KF_F32;
     constexpr int GB = 8, RB = kBinSlice / 64;
     int n_items;
     const int n_it = (int)((bin_len + kBinSlice - 1) / kBinSlice);
@@ -1316,7 +1388,6 @@ __device__ __forceinline__ void slice_block(const SliceArgs& a, const int b) {
     // block: the blocks then read neighbouring segments of the same spikes
     // at about the same time.  The barrier after a chunk's descriptors also
     // makes the window zeroing visible to the walk.
-    constexpr int G = SynGroup<WF>::n;
     __shared__ int s_next;  // next unclaimed spike of the chunk
     uint64_t ev = 0;
     int64_t total = 0;
@@ -1359,143 +1430,15 @@ __device__ __forceinline__ void slice_block(const SliceArgs& a, const int b) {
       if (c0 == 0 && tid < kMaxThr) thr[tid] = thr_v;
       if (tid == 0) s_next = 0;
       __syncthreads();
-      // (2) waves take groups of G spikes from a shared counter until the
-      // chunk is done (a wave slowed by issue priority or memory latency
-      // simply takes fewer groups).  G loads issue back to back (lanes past
-      // a segment's end and slots past the chunk read record 0, unused),
-      // then the adds; the group bound is uniform.
-      for (;;) {
-        int g0 = 0;
-        if (lane == 0)
-          g0 = __hip_atomic_fetch_add(&s_next, G, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        g0 = __builtin_amdgcn_readfirstlane(g0);
-        if (g0 >= n_c) break;
-        const int n_here = (n_c - g0) < G ? (n_c - g0) : G;
-        SynRaw<WF> raw[G];
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-          const uint2 d = desc[g0 + u];  // past the share: stale or padding, masked
-          // the start also enters the predicate, so both halves are read
-          // unconditionally (no per-slot branch around the LDS read)
-          const bool on = (u < n_here) & (lane < (int)d.y) & (d.x != 0xffffffffu);
-          raw[u] = syn_fetch<WF>(a.syn, a.syn_dly, on ? d.x + (uint32_t)lane : 0u);
-        }
-        // ALU work while the loads are in flight
+      // (2) the chunk's segments
+      auto drive_next = [&]() {
         if (rounds_done < n_rounds) drive_round(rounds_done++);
-        uint32_t mt[G];
-        bool any_long = false;
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-          mt[u] = meta[g0 + u];
-          any_long |= (mt[u] & 127u) > 64u;  // unconditional use: no sinking
-        }
-        if constexpr (PL) {
-          // plastic: each lane's synapse takes the entry's spikes in lag
-          // order, its weight updated before each add and stored back
-          const int32_t T = (int32_t)w_lo;
-          const int32_t t0s = (int32_t)(w_lo - Dmin);
-#pragma unroll
-          for (int u = 0; u < G; ++u) {
-            const uint32_t m = __builtin_amdgcn_readfirstlane(mt[u]);
-            const uint32_t lm = __builtin_amdgcn_readfirstlane(lagm[g0 + u]);
-            const int32_t tp0 = __builtin_amdgcn_readfirstlane(tpv[g0 + u]);
-            const uint32_t sx = __builtin_amdgcn_readfirstlane(desc[g0 + u].x);
-            const bool inh = (int32_t)m < 0;
-            const float m1 = inh ? a.wm1_i : a.wm1_e;
-            if ((u < n_here) & (lane < (int)(m & 127u)) & (lane < 64)) {
-              if constexpr (WF == WF_FP32) {
-                float w = __uint_as_float((uint32_t)raw[u].r);
-                const int jl = (int)(raw[u].r >> 32) - (int)j0;
-                const int dd = (int)raw[u].d;
-                if (inh) {
-                  const int v = (int)(m1 * w);
-                  uint32_t lmi = lm;
-                  while (lmi) {
-                    const int l = __ffs(lmi) - 1;
-                    lmi &= lmi - 1;
-                    __hip_atomic_fetch_add((unsigned long long*)&win[(l + dd - Dmin) * B + jl],
-                                           (unsigned long long)(long long)v, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-                  }
-                } else {
-                  w = plastic_walk(a, w, dd, pm[jl], pb[jl], lm, tp0, t0s, T, Dmin, B, jl, win,
-                                   m1);
-                  ((uint32_t*)a.syn)[2 * (size_t)(sx + (uint32_t)lane)] = __float_as_uint(w);
-                }
-              }
-            }
-          }
-        } else {
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-          // the meta word is uniform: population constants and the lag row
-          // come out of scalar registers
-          const uint32_t m = __builtin_amdgcn_readfirstlane(mt[u]);
-          const uint32_t sel = (uint32_t)((int32_t)m >> 31);  // all ones: inhibitory
-          const float m0 = __uint_as_float((__float_as_uint(a.wm0_e) & ~sel) |
-                                           (__float_as_uint(a.wm0_i) & sel));
-          const float m1 = __uint_as_float((__float_as_uint(a.wm1_e) & ~sel) |
-                                           (__float_as_uint(a.wm1_i) & sel));
-          long long* row = win + ((m >> 7) & 0xffffffu);
-          if ((u < n_here) & (lane < (int)(m & 127u))) {
-            int slot, v;
-            syn_decode<WF>(raw[u], (int32_t)j0, Dmin, B, m0, m1, slot, v);
-            __hip_atomic_fetch_add((unsigned long long*)&row[slot], (unsigned long long)(long long)v,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          }
-        }
-        }  // static synapses
-        // segments longer than one wave (rare: a block's share of a source's
-        // targets is ~K/NB)
-        if (__builtin_amdgcn_readfirstlane((int)any_long)) {
-          for (int u = 0; u < n_here; ++u) {
-            const uint2 d = desc[g0 + u];
-            const uint32_t m = meta[g0 + u];
-            const int sl = __builtin_amdgcn_readfirstlane((int)d.y);
-            const bool inh = (int)m < 0;
-            for (int e0 = 64; e0 < sl; e0 += 64) {
-              const bool on = lane + e0 < sl;
-              const SynRaw<WF> x =
-                  syn_fetch<WF>(a.syn, a.syn_dly, on ? d.x + (uint32_t)(e0 + lane) : 0u);
-              if constexpr (PL && WF == WF_FP32) {
-                if (on) {
-                  const uint32_t lm = lagm[g0 + u];
-                  float w = __uint_as_float((uint32_t)x.r);
-                  const int jl = (int)(x.r >> 32) - (int)j0;
-                  const int dd = (int)x.d;
-                  const float m1 = inh ? a.wm1_i : a.wm1_e;
-                  if (inh) {
-                    const int v = (int)(m1 * w);
-                    uint32_t lmi = lm;
-                    while (lmi) {
-                      const int l = __ffs(lmi) - 1;
-                      lmi &= lmi - 1;
-                      __hip_atomic_fetch_add((unsigned long long*)&win[(l + dd - Dmin) * B + jl],
-                                             (unsigned long long)(long long)v, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_WORKGROUP);
-                    }
-                  } else {
-                    w = plastic_walk(a, w, dd, pm[jl], pb[jl], lm, tpv[g0 + u],
-                                     (int32_t)(w_lo - Dmin), (int32_t)w_lo, Dmin, B, jl, win, m1);
-                    ((uint32_t*)a.syn)[2 * (size_t)(d.x + (uint32_t)(e0 + lane))] =
-                        __float_as_uint(w);
-                  }
-                }
-                continue;
-              }
-              if (on) {
-                int slot, v;
-                syn_decode<WF>(x, (int32_t)j0, Dmin, B, inh ? a.wm0_i : a.wm0_e,
-                               inh ? a.wm1_i : a.wm1_e, slot, v);
-                __hip_atomic_fetch_add(
-                    (unsigned long long*)&win[(int)((m >> 7) & 0xffffffu) + slot],
-                    (unsigned long long)(long long)v, __ATOMIC_RELAXED,
-                    __HIP_MEMORY_SCOPE_WORKGROUP);
-              }
-            }
-          }
-        }
-      }
+      };
+      if constexpr (PL)
+        walk_plastic(a, desc, meta, lagm, tpv, pm, pb, n_c, &s_next, win, w_lo, Dmin, B, lane,
+                     drive_next);
+      else
+        walk_chunk<KF>(a, desc, meta, n_c, &s_next, win, lane, drive_next);
       __syncthreads();  // the next chunk overwrites the descriptors
     }
     if (total == 0) {  // no chunk stored the thresholds or made the zeroing visible
@@ -1853,13 +1796,13 @@ __device__ __forceinline__ void touch_lines(const T* p) {
 // lines in its L2.  Arguments live in device memory, so the compiler loads
 // fields where they are used instead of holding the whole struct in
 // scalar registers.
-template <int WF>
+template <int KF>
 __global__ void __launch_bounds__(kSliceThreads)
     k_slice(const SliceArgs* __restrict__ args, const int2* __restrict__ map) {
   const int2 m = map[blockIdx.x];
   if (m.x < 0) return;
   touch_lines(args + m.x);
-  slice_block<WF, false, false>(args[m.x], m.y);
+  slice_block<KF, false, false>(args[m.x], m.y);
 }
 
 // One network: the arguments travel by value in the kernel-argument segment
@@ -1870,14 +1813,14 @@ struct SingleArgs {
   SliceArgs a;
   int32_t per_xcd;
 };
-template <int WF, bool BIN, bool DYN, bool PL = false>
+template <int KF, bool BIN, bool DYN, bool PL = false>
 __global__ void __launch_bounds__(kSliceThreads) k_slice1(SingleArgs s) {
   const SingleArgs* p = (const SingleArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   touch_lines(p);
   const int gx = blockIdx.x;
   const int b = (gx & 7) * p->per_xcd + (gx >> 3);
   if (b >= p->a.NB) return;
-  slice_block<WF, BIN, DYN, PL>(p->a, b);
+  slice_block<KF, BIN, DYN, PL>(p->a, b);
 }
 
 // ---------------------------------------------------------------------------
@@ -1983,7 +1926,7 @@ bool persist_plan(int32_t B, int32_t Dmin, int32_t Dmax, size_t budget, PersistP
 // flush are therefore loops over rows with the next row's reads in flight,
 // and spikes are collected as a mask of steps per neuron and listed in one
 // loop after the update.
-template <int WF, bool CL>
+template <int KF, bool CL>
 __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
   const PersistArgs* pp = (const PersistArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   touch_lines(pp);
@@ -2262,7 +2205,7 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
         total = s_tot;
       }
       const int n_c = (int)(total - c0 < CAP ? total - c0 : CAP);
-      walk_chunk<WF>(a, desc, meta, n_c, &s_next, win, (int32_t)j0, Dmin, B, lane);
+      walk_chunk<KF>(a, desc, meta, n_c, &s_next, win, lane, [] {});
       __syncthreads();  // window adds and drive counts complete
       if (c0 + CAP >= total) break;
     }
@@ -2648,50 +2591,27 @@ hipError_t launch_slice(hipStream_t s, const SliceArgs* d_args, const int2* d_ma
                         int32_t n_blocks, size_t lds, int wform) {
   if (n_blocks <= 0) return hipSuccess;
   const dim3 grid((unsigned)n_blocks), block(kSliceThreads);
-  switch (wform) {
-    case WF_FP32:
-      hipLaunchKernelGGL(k_slice<WF_FP32>, grid, block, lds, s, d_args, d_map);
-      break;
-    case WF_BF16:
-      hipLaunchKernelGGL(k_slice<WF_BF16>, grid, block, lds, s, d_args, d_map);
-      break;
-    case WF_PACKED:
-      hipLaunchKernelGGL(k_slice<WF_PACKED>, grid, block, lds, s, d_args, d_map);
-      break;
-    default:
-      hipLaunchKernelGGL(k_slice<WF_BF16_RESID>, grid, block, lds, s, d_args, d_map);
-      break;
-  }
+  if (wform == WF_FP32)
+    hipLaunchKernelGGL(k_slice<KF_F32>, grid, block, lds, s, d_args, d_map);
+  else
+    hipLaunchKernelGGL(k_slice<KF_16>, grid, block, lds, s, d_args, d_map);
   return hipGetLastError();
 }
 
 template <bool DYN>
 void launch_slice1_as(hipStream_t s, const SingleArgs& sa, size_t lds, int wform) {
   const dim3 grid((unsigned)(8 * sa.per_xcd)), block(kSliceThreads);
-  if (sa.a.plastic) {  // plastic synapses: FP32 block-major only
-    hipLaunchKernelGGL((k_slice1<WF_FP32, false, DYN, true>), grid, block, lds, s, sa);
-    return;
-  }
-  if (sa.a.bins) {
-    // binned records: 8 bytes (FP32 weight) or 4 (BF16 bits)
-    if (wform == WF_FP32) hipLaunchKernelGGL((k_slice1<WF_FP32, true, DYN>), grid, block, lds, s, sa);
-    else hipLaunchKernelGGL((k_slice1<WF_BF16, true, DYN>), grid, block, lds, s, sa);
-    return;
-  }
-  switch (wform) {
-    case WF_FP32:
-      hipLaunchKernelGGL((k_slice1<WF_FP32, false, DYN>), grid, block, lds, s, sa);
-      break;
-    case WF_BF16:
-      hipLaunchKernelGGL((k_slice1<WF_BF16, false, DYN>), grid, block, lds, s, sa);
-      break;
-    case WF_PACKED:
-      hipLaunchKernelGGL((k_slice1<WF_PACKED, false, DYN>), grid, block, lds, s, sa);
-      break;
-    default:
-      hipLaunchKernelGGL((k_slice1<WF_BF16_RESID, false, DYN>), grid, block, lds, s, sa);
-      break;
-  }
+  const bool f32 = wform == WF_FP32;
+  if (sa.a.plastic)  // plastic synapses: FP32 block-major only
+    hipLaunchKernelGGL((k_slice1<KF_F32, false, DYN, true>), grid, block, lds, s, sa);
+  else if (sa.a.bins && f32)  // binned records: 8 bytes (FP32 weight) or 4 (BF16 bits)
+    hipLaunchKernelGGL((k_slice1<KF_F32, true, DYN>), grid, block, lds, s, sa);
+  else if (sa.a.bins)
+    hipLaunchKernelGGL((k_slice1<KF_16, true, DYN>), grid, block, lds, s, sa);
+  else if (f32)
+    hipLaunchKernelGGL((k_slice1<KF_F32, false, DYN>), grid, block, lds, s, sa);
+  else
+    hipLaunchKernelGGL((k_slice1<KF_16, false, DYN>), grid, block, lds, s, sa);
 }
 
 hipError_t launch_slice1(hipStream_t s, const SliceArgs& a, size_t lds, int wform) {
@@ -2706,12 +2626,9 @@ hipError_t launch_slice1(hipStream_t s, const SliceArgs& a, size_t lds, int wfor
 
 // The kernel of a weight form and carry placement.
 const void* persist_kernel(int wform, bool cl) {
-  switch (wform) {
-    case WF_FP32: return cl ? (const void*)k_persist<WF_FP32, true> : (const void*)k_persist<WF_FP32, false>;
-    case WF_BF16: return cl ? (const void*)k_persist<WF_BF16, true> : (const void*)k_persist<WF_BF16, false>;
-    case WF_PACKED: return cl ? (const void*)k_persist<WF_PACKED, true> : (const void*)k_persist<WF_PACKED, false>;
-    default: return cl ? (const void*)k_persist<WF_BF16_RESID, true> : (const void*)k_persist<WF_BF16_RESID, false>;
-  }
+  if (wform == WF_FP32)
+    return cl ? (const void*)k_persist<KF_F32, true> : (const void*)k_persist<KF_F32, false>;
+  return cl ? (const void*)k_persist<KF_16, true> : (const void*)k_persist<KF_16, false>;
 }
 
 // Workgroups per CU that a persistent launch of this weight form can hold.
