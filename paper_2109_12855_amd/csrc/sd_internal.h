@@ -215,8 +215,10 @@ hipError_t launch_slice(hipStream_t s, const SliceArgs* d_args, const int2* d_ma
 hipError_t launch_slice1(hipStream_t s, const SliceArgs& a, size_t lds, int wform);
 // persistent slices: LDS plan of a block size, and one launch of S slices
 struct PersistPlan {
+  bool helpers;     // waves without a neuron work during the update
   bool carry_lds;   // sums of later steps in LDS (else in the HBM ring)
   int32_t drows;    // drive-count rows
+  int32_t crows;    // carry rows in LDS
   int32_t cap;      // spikes per walk chunk
   size_t lds;
 };

@@ -45,6 +45,19 @@ namespace sd {
 // Philox4x64-10 (Salmon et al., SC'11); counter (c0, c1, 0, 0), key (seed,
 // stream).  Device-only implementation.
 // ---------------------------------------------------------------------------
+// The 128-bit product a * b from four 32-bit multiply-adds, the most a wave
+// issues at quarter rate here: asked for as a high and a low product the
+// compiler adds two multiplies for the low one.
+__device__ __forceinline__ void mul_wide(uint64_t a, uint64_t b, uint64_t& hi, uint64_t& lo) {
+  const uint32_t al = (uint32_t)a, ah = (uint32_t)(a >> 32);
+  const uint32_t bl = (uint32_t)b, bh = (uint32_t)(b >> 32);
+  const uint64_t t0 = (uint64_t)al * bl;
+  const uint64_t t1 = (uint64_t)ah * bl + (t0 >> 32);
+  const uint64_t t2 = (uint64_t)al * bh + (uint32_t)t1;
+  hi = (uint64_t)ah * bh + (t1 >> 32) + (t2 >> 32);
+  lo = (t2 << 32) | (uint32_t)t0;
+}
+
 __device__ __forceinline__ void philox(uint64_t seed, uint64_t stream, uint64_t c0, uint64_t c1,
                                        uint64_t out[4]) {
   constexpr uint64_t M0 = 0xD2E7470EE14C6C93ULL, M1 = 0xCA5A826395121157ULL;
@@ -52,8 +65,9 @@ __device__ __forceinline__ void philox(uint64_t seed, uint64_t stream, uint64_t 
   uint64_t x0 = c0, x1 = c1, x2 = 0, x3 = 0, k0 = seed, k1 = stream;
 #pragma unroll
   for (int i = 0; i < 10; ++i) {
-    const uint64_t hi0 = __umul64hi(M0, x0), lo0 = M0 * x0;
-    const uint64_t hi1 = __umul64hi(M1, x2), lo1 = M1 * x2;
+    uint64_t hi0, lo0, hi1, lo1;
+    mul_wide(M0, x0, hi0, lo0);
+    mul_wide(M1, x2, hi1, lo1);
     const uint64_t n0 = hi1 ^ x1 ^ k0, n2 = hi0 ^ x3 ^ k1;
     x0 = n0;
     x1 = lo1;
@@ -897,6 +911,15 @@ __device__ __forceinline__ void drive_counts(const uint64_t rr[4], const uint32_
 
 template <bool V> struct BoolC { static constexpr bool value = V; };
 
+// Uniform values read inside a loop over LDS data, held in vector registers:
+// short of scalar registers the compiler reads an argument again at each use,
+// and the wait for that scalar load also waits for the LDS operations before
+// it (both count against one counter).
+__device__ __forceinline__ float in_vgpr(float x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 // A thread keeps the staged HBM ring rows of its own neuron in registers
 // when every neuron has its own thread and a slice has at most this many
 // steps; otherwise they are staged in LDS.
@@ -990,6 +1013,8 @@ __device__ __forceinline__ void walk_chunk(const SliceArgs& a, const uint2* desc
                                            const uint32_t* meta, int n_c, int* s_next,
                                            long long* win, int lane, F in_flight) {
   constexpr int G = SynGroup<KF>::n;
+  const float m0e = in_vgpr(a.wm0_e), m0i = in_vgpr(a.wm0_i);
+  const float m1e = in_vgpr(a.wm1_e), m1i = in_vgpr(a.wm1_i);
   for (;;) {
     int g0 = 0;
     if (lane == 0)
@@ -1015,11 +1040,8 @@ __device__ __forceinline__ void walk_chunk(const SliceArgs& a, const uint2* desc
 #pragma unroll
     for (int u = 0; u < G; ++u) {
       const uint32_t m = __builtin_amdgcn_readfirstlane(mt[u]);
-      const uint32_t sel = (uint32_t)((int32_t)m >> 31);  // all ones: inhibitory
-      const float m0 = __uint_as_float((__float_as_uint(a.wm0_e) & ~sel) |
-                                       (__float_as_uint(a.wm0_i) & sel));
-      const float m1 = __uint_as_float((__float_as_uint(a.wm1_e) & ~sel) |
-                                       (__float_as_uint(a.wm1_i) & sel));
+      const bool inh = (int32_t)m < 0;
+      const float m0 = inh ? m0i : m0e, m1 = inh ? m1i : m1e;
       long long* row = win + ((m >> 7) & 0xffffffu);
       if ((u < n_here) & (lane < (int)(m & 127u))) {
         int slot, v;
@@ -1040,7 +1062,7 @@ __device__ __forceinline__ void walk_chunk(const SliceArgs& a, const uint2* desc
           const SynRaw<KF> x = syn_fetch<KF>(a.syn, on ? d.x + (uint32_t)(e0 + lane) : 0u);
           if (on) {
             int slot, v;
-            syn_decode<KF>(x, inh ? a.wm0_i : a.wm0_e, inh ? a.wm1_i : a.wm1_e, slot, v);
+            syn_decode<KF>(x, inh ? m0i : m0e, inh ? m1i : m1e, slot, v);
             __hip_atomic_fetch_add((unsigned long long*)&win[(int)((m >> 7) & 0xffffffu) + slot],
                                    (unsigned long long)(long long)v, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1850,9 +1872,10 @@ __global__ void __launch_bounds__(kSliceThreads) k_slice1(SingleArgs s) {
 // block's part of the slice's list buffer, between a release and an acquire
 // fence.
 // Per slice, one launch per slice against this kernel (stretches of 20 to 100
-// slices): 1,250-neuron delta net 14.9 -> 9.6 us, 30,011 alpha neurons 22.5 ->
-// 15, 112,500 packed 32.8 -> 22.5, FP32 37.6 -> 28, one-step slices 20.5 ->
-// 8.6.
+// slices): 1,250-neuron delta net 14.9 -> 7.4 us, 30,011 alpha neurons 22.5 ->
+// 13, 112,500 packed 32.8 -> 22, FP32 37.6 -> 25, one-step slices 20.5 -> 8.7.
+// Three polls in flight instead of one were 2% slower, spike groups split
+// evenly over the waves 1-3%.
 constexpr int64_t kBarSpin = 1LL << 22;  // polls before a wait gives up (explicit mode)
 constexpr int kXchWords = 32;            // 64-bit words of a block's line
 constexpr int kXchPoll = 4;              // words of a line read by the first poll
@@ -1872,6 +1895,8 @@ struct PersistArgs {
   int32_t per_xcd;     // blocks per XCD (grid = 8 * per_xcd)
   int32_t cap;         // spikes per walk chunk
   int32_t drows;       // drive-count rows (d_min, or whole 8-step chunks)
+  int32_t crows;       // carry rows in LDS
+  int32_t helpers;     // waves without a neuron draw the drive during the update
   uint32_t epoch0;     // tag of slice 0's line
   int64_t t0;          // first step of slice 0
   int64_t rb_hi0;      // HBM ring rows of steps below this hold earlier sums
@@ -1883,13 +1908,13 @@ struct PersistArgs {
 struct PersistLds {
   size_t win, carry, dcnt, thr, pub, desc, meta, total;
 };
-__host__ __device__ inline PersistLds persist_lds_layout(int B, int Dmin, int Dmax, int drows,
-                                                         bool carry_lds, int cap) {
+__host__ __device__ inline PersistLds persist_lds_layout(int B, int Dmax, int drows, int crows,
+                                                         int cap) {
   auto up = [](size_t x) { return (x + 15) / 16 * 16; };
   PersistLds L;
   size_t o = 0;
   L.win = o;   o = up(o + (size_t)Dmax * B * 8);
-  L.carry = o; o = up(o + (carry_lds ? (size_t)(Dmax - Dmin) * B * 4 : 0));
+  L.carry = o; o = up(o + (size_t)crows * B * 4);
   L.dcnt = o;  o = up(o + (size_t)drows * B);
   L.thr = o;   o = up(o + (size_t)kMaxThr * 4);
   L.pub = o;   o = up(o + (size_t)kPubCap * 2);
@@ -1899,21 +1924,25 @@ __host__ __device__ inline PersistLds persist_lds_layout(int B, int Dmin, int Dm
   return L;
 }
 
-// The largest configuration that fits the LDS: carry rows in LDS before the
-// HBM ring, drive counts kept for whole 8-step chunks before recomputed per
-// slice, then as many spikes per walk chunk as fit (at most 2048).
+// The largest configuration that fits the LDS.  First choice: the waves
+// without a neuron draw the next slice's drive while the others update, which
+// needs drive rows of two slices and pays from six such waves (blocks of at
+// most 640 neurons: with fewer the update waits for them).  Then carry rows
+// in LDS before the HBM ring, and drive counts kept for whole 8-step chunks
+// before drawn again per slice.  Walk chunks take what is left, at most 2048
+// spikes.
 bool persist_plan(int32_t B, int32_t Dmin, int32_t Dmax, size_t budget, PersistPlan* plan) {
-  const int32_t ring = (Dmin + 14) / 8 * 8;
-  for (int k = 0; k < 4; ++k) {
+  for (int k = B <= kSliceThreads - 6 * 64 ? 0 : 1; k < 5; ++k) {
     PersistPlan p;
-    p.carry_lds = (k & 1) == 0;
-    p.drows = (k & 2) == 0 ? ring : Dmin;
-    const size_t base = persist_lds_layout(B, Dmin, Dmax, p.drows, p.carry_lds, 0).total;
-    const size_t least = persist_lds_layout(B, Dmin, Dmax, p.drows, p.carry_lds, 256).total;
-    if (least > budget) continue;
+    p.helpers = k == 0;
+    p.carry_lds = k == 0 || k == 1 || k == 3;
+    p.drows = k == 0 ? (2 * Dmin + 14) / 8 * 8 : k < 3 ? (Dmin + 14) / 8 * 8 : Dmin;
+    p.crows = p.carry_lds ? Dmax - Dmin : 0;
+    const size_t base = persist_lds_layout(B, Dmax, p.drows, p.crows, 0).total;
+    if (persist_lds_layout(B, Dmax, p.drows, p.crows, 256).total > budget) continue;
     p.cap = (int32_t)std::min<size_t>(2048, (budget - base - 32) / 12 / 64 * 64);
     p.cap = std::max(p.cap, 256);
-    p.lds = persist_lds_layout(B, Dmin, Dmax, p.drows, p.carry_lds, p.cap).total;
+    p.lds = persist_lds_layout(B, Dmax, p.drows, p.crows, p.cap).total;
     *plan = p;
     return true;
   }
@@ -1923,9 +1952,8 @@ bool persist_plan(int32_t B, int32_t Dmin, int32_t Dmax, size_t budget, PersistP
 // The code of a slice runs once per slice, so its size counts: unrolled to
 // ~70 KB it ran from the L2 through the 64 KB instruction cache that two
 // compute units share (~0.8 us per step of the update).  The update and the
-// flush are therefore loops over rows with the next row's reads in flight,
-// and spikes are collected as a mask of steps per neuron and listed in one
-// loop after the update.
+// flush are therefore loops of four rows, and spikes are collected as a mask
+// of steps per neuron and listed in one loop after the update.
 template <int KF, bool CL>
 __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
   const PersistArgs* pp = (const PersistArgs*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -1939,12 +1967,12 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
   const int NB = a.NB;
   if (b >= NB) return;
   const int B = a.B, Dmin = a.Dmin, Dmax = a.Dmax, R = Dmax - Dmin;
-  const int CAP = pp->cap, drows = pp->drows;
+  const int CAP = pp->cap, drows = pp->drows, crows = pp->crows;
   const bool dring = drows != Dmin;  // drive counts kept for whole chunks, row t % drows
   const int64_t N = a.N;
   const int64_t j0 = (int64_t)b * B;
   const int nb = (int)((N - j0) < B ? (N - j0) : B);
-  const PersistLds Lo = persist_lds_layout(B, Dmin, Dmax, drows, CL, CAP);
+  const PersistLds Lo = persist_lds_layout(B, Dmax, drows, crows, CAP);
   long long* win = (long long*)(lds_raw + Lo.win);
   float* carry = (float*)(lds_raw + Lo.carry);
   uint8_t* dcnt = lds_raw + Lo.dcnt;
@@ -1973,7 +2001,7 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
   const int64_t gn = j0 + (own ? tid : 0);
   float V = 0.f, y1 = 0.f, y2 = 0.f;
   int rf = 0;
-  int cb = R > 0 ? (int)(t0 % R) : 0;  // carry row of step w_lo
+  int cb = 0;                          // carry row of step w_lo
   int lb = (int)(t0 % a.L);            // HBM ring row of step w_lo
   if (own) {
     V = a.V[gn];
@@ -1983,25 +2011,54 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
       y2 = a.y2[gn];
     }
     for (int q = 0; q < R; ++q) {
-      int lr = lb + q, row = cb + q;
+      int lr = lb + q;
       if (lr >= a.L) lr -= a.L;
-      if (row >= R) row -= R;
       float* cell = a.rb + (int64_t)lr * N + gn;
-      if constexpr (CL) carry[row * B + tid] = t0 + q < pp->rb_hi0 ? *cell : 0.f;
+      if constexpr (CL) carry[q * B + tid] = t0 + q < pp->rb_hi0 ? *cell : 0.f;
       else if (t0 + q >= pp->rb_hi0) *cell = 0.f;
     }
   }
   unsigned long long spk_all = 0, in_all = 0, ev = 0;
   const int S = pp->S;
-  const float inv = a.fx_inv;
+  const float inv = in_vgpr(a.fx_inv);
 
-  // Philox drive counts of a slice's steps: one block per (neuron, 8-step
-  // chunk); a chunk that reaches past the slice is kept for the next one
-  // (dring) or drawn again.  Groups of nb threads take a chunk each.
-  const int dgrp = kSliceThreads / nb;
-  const int dsub = tid / nb, dn = tid - dsub * nb;
+  // With helpers, the waves without a neuron draw the next slice's drive
+  // while the others update; else every thread does so after the spikes are
+  // published.
+  const int n_upd_t = (nb + 63) & ~63;  // threads of the updating waves
+  const bool helpers = pp->helpers && n_upd_t < kSliceThreads;
   int64_t chunk_done = (t0 >> 3) - 1;      // chunks drawn so far (dring)
   int db = dring ? (int)(t0 % drows) : 0;  // drive-count row of step w_lo
+
+  // Philox drive counts of the steps [w, w + Dmin), w's row wrow: one block
+  // per (neuron, 8-step chunk), shared out over n threads of index i0; a chunk
+  // that reaches past the slice is kept for the next one (dring) or drawn
+  // again.
+  auto drive = [&](int64_t w, int wrow, int i0, int n) {
+    const int64_t c1 = (w + Dmin - 1) >> 3;
+    const int64_t c0 = dring ? chunk_done + 1 : w >> 3;
+    const int n_ch = (int)(c1 - c0 + 1), row0 = wrow + (int)(c0 * 8 - w);
+    chunk_done = c1;
+    int dn = i0, ci = 0;
+    for (;;) {
+      while (dn >= nb) {
+        dn -= nb;
+        ++ci;
+      }
+      if (ci >= n_ch) break;
+      uint64_t rr[4];
+      uint32_t cnt[8];
+      philox(a.seed, STREAM_DRIVE, (uint64_t)(j0 + dn), (uint64_t)(c0 + ci), rr);
+      drive_counts(rr, thr, n_thr, cnt);
+      int row = row0 + ci * 8;
+      if (dring)
+        while (row >= drows) row -= drows;
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (dring || (row + q >= 0 && row + q < Dmin)) dcnt[(row + q) * B + dn] = (uint8_t)cnt[q];
+      dn += n;
+    }
+  };
 
   // one spike at a position of the walk chunk: descriptor of its segment in
   // this block
@@ -2052,28 +2109,8 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
     const uint32_t tag = (pp->epoch0 + (uint32_t)k) & 0xffffu;  // of this slice's spikes
     uint32_t* const ilist = pp->lists[cur];
     uint32_t* const olist = pp->lists[cur ^ 1];
-    // ---- drive counts (while the other blocks' lines arrive) ---------------
-    {
-      const int64_t c1 = (w_lo + Dmin - 1) >> 3;
-      const int64_t c0 = dring ? chunk_done + 1 : w_lo >> 3;
-      const int n_ch = (int)(c1 - c0 + 1), row0 = db + (int)(c0 * 8 - w_lo);
-      chunk_done = c1;
-      if (dsub < dgrp) {
-        for (int ci = dsub; ci < n_ch; ci += dgrp) {
-          uint64_t rr[4];
-          uint32_t cnt[8];
-          philox(a.seed, STREAM_DRIVE, (uint64_t)(j0 + dn), (uint64_t)(c0 + ci), rr);
-          drive_counts(rr, thr, n_thr, cnt);
-          int row = row0 + ci * 8;
-          if (dring)
-            while (row >= drows) row -= drows;
-#pragma unroll
-          for (int q = 0; q < 8; ++q)
-            if (dring || (row + q >= 0 && row + q < Dmin))
-              dcnt[(row + q) * B + dn] = (uint8_t)cnt[q];
-        }
-      }
-    }
+    // drive counts, unless the helpers drew them during the last update
+    if (k == 0 || !helpers) drive(w_lo, db, tid, kSliceThreads);
     // ---- delivery of the slice before into the window ---------------------
     int64_t total = 0;
     if (k == 0 && pp->pend0) {
@@ -2216,52 +2253,79 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
     }
     // ---- update of the slice's steps ---------------------------------------
     const bool last = k + 1 == S;
-    if (own) {
-      const float P11 = a.prop[0], P21 = a.prop[1], P22 = a.prop[2], P31 = a.prop[3];
-      const float P32 = a.prop[4], P33 = a.prop[5], P30Ie = a.prop[6], insc = a.prop[7];
-      const float drive_w = a.drive_w, e_l = a.e_l, v_th = a.v_th, v_reset = a.v_reset;
-      const int ref_steps = a.ref_steps;
-      const bool delta = a.model == MODEL_DELTA;
-      int dr = db, cr = cb, lr = lb;
-      auto read_row = [&](int s, long long& wq, uint32_t& dc, float& cv) {
-        wq = win[s * B + tid];
-        dc = dcnt[dr * B + tid];
-        cv = 0.f;
-        if (s < R) {
-          if constexpr (CL) cv = carry[cr * B + tid];
-          else cv = a.rb[(int64_t)lr * N + gn];
-        }
-        if (++dr == drows) dr = 0;
-        if (++cr >= R) cr = 0;
-        if (++lr == a.L) lr = 0;
-      };
-      uint32_t fired = 0;
-      long long wq;
-      uint32_t dc;
-      float cv;
-      read_row(0, wq, dc, cv);
-#pragma unroll 1
-      for (int s = 0; s < Dmin; ++s) {
-        const float in = cv + from_fixed(wq, inv);
-        const float drv = (float)dc * drive_w;
-        win[s * B + tid] = 0;
-        if (s + 1 < Dmin) read_row(s + 1, wq, dc, cv);
-        if (delta) {
-          const float Vn = e_l + P33 * (V - e_l) + P30Ie + in + drv;
-          V = rf > 0 ? V : Vn;
-        } else {
-          const float Vn = e_l + P31 * y1 + P32 * y2 + P33 * (V - e_l) + P30Ie;
-          V = rf > 0 ? V : Vn;
-          const float y2n = P21 * y1 + P22 * y2;
-          y1 = P11 * y1 + insc * (in + drv);
-          y2 = y2n;
-        }
-        rf = rf > 0 ? rf - 1 : 0;
-        const bool spk = V >= v_th;
-        V = spk ? v_reset : V;
-        rf = spk ? ref_steps : rf;
-        fired |= (uint32_t)spk << s;
+    if (helpers && !last) {
+      if (tid >= n_upd_t) {
+        int dnx = db + Dmin;
+        while (dnx >= drows) dnx -= drows;
+        drive(w_lo + Dmin, dnx, tid - n_upd_t, kSliceThreads - n_upd_t);
+      } else {
+        chunk_done = (w_lo + 2 * Dmin - 1) >> 3;  // as the helpers leave it
       }
+    }
+    if (own) {
+      uint32_t fired = 0;
+      // four steps at a time: their rows' reads first, then their inputs,
+      // then the recurrence
+      auto steps = [&](auto delta_tag) {
+        constexpr bool kDelta = decltype(delta_tag)::value;
+        const float P11 = in_vgpr(a.prop[0]), P21 = in_vgpr(a.prop[1]), P22 = in_vgpr(a.prop[2]);
+        const float P31 = in_vgpr(a.prop[3]), P32 = in_vgpr(a.prop[4]), P33 = in_vgpr(a.prop[5]);
+        const float P30Ie = in_vgpr(a.prop[6]), insc = in_vgpr(a.prop[7]);
+        const float drive_w = in_vgpr(a.drive_w), e_l = in_vgpr(a.e_l);
+        const float v_th = in_vgpr(a.v_th), v_reset = in_vgpr(a.v_reset);
+        const int ref_steps = a.ref_steps;
+        int dr = db, cr = cb, lr = lb;
+#pragma unroll 1
+        for (int s0 = 0; s0 < Dmin; s0 += 4) {
+          long long wq[4];
+          uint32_t dc[4];
+          float in[4], drv[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int s = s0 + i < Dmin ? s0 + i : Dmin - 1;
+            wq[i] = win[s * B + tid];
+            dc[i] = dcnt[dr * B + tid];
+            in[i] = 0.f;
+            if (s < R) {
+              if constexpr (CL) in[i] = carry[cr * B + tid];
+              else in[i] = a.rb[(int64_t)lr * N + gn];
+            }
+            if (s0 + i + 1 < Dmin) {
+              if (++dr == drows) dr = 0;
+              if (++cr >= crows) cr = 0;
+              if (++lr == a.L) lr = 0;
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            in[i] += from_fixed(wq[i], inv);
+            drv[i] = (float)dc[i] * drive_w;
+            win[(s0 + i < Dmin ? s0 + i : Dmin - 1) * B + tid] = 0;
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if (s0 + i >= Dmin) break;
+            if constexpr (kDelta) {
+              const float Vn = e_l + P33 * (V - e_l) + P30Ie + in[i] + drv[i];
+              V = rf > 0 ? V : Vn;
+            } else {
+              const float Vn = e_l + P31 * y1 + P32 * y2 + P33 * (V - e_l) + P30Ie;
+              V = rf > 0 ? V : Vn;
+              const float y2n = P21 * y1 + P22 * y2;
+              y1 = P11 * y1 + insc * (in[i] + drv[i]);
+              y2 = y2n;
+            }
+            rf = rf > 0 ? rf - 1 : 0;
+            const bool spk = V >= v_th;
+            V = spk ? v_reset : V;
+            rf = spk ? ref_steps : rf;
+            fired |= (uint32_t)spk << (s0 + i);
+          }
+        }
+      };
+      if (a.model == MODEL_DELTA) steps(BoolC<true>{});
+      else steps(BoolC<false>{});
       // ---- new spikes to the block's LDS list ------------------------------
 #pragma unroll 1
       while (fired) {
@@ -2341,40 +2405,52 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
       }
     }
     if (tid == 0) spk_all += (unsigned long long)n_spk;
-    // ---- rows due later: rounded once and added to the carried sums -------
-    if (own) {
-      int row = cb + Dmin, lr = lb + Dmin;
-      while (R > 0 && row >= R) row -= R;
-      if (lr >= a.L) lr -= a.L;
-#pragma unroll 1
-      for (int q0 = Dmin; q0 < Dmax; q0 += 4) {
-        // four rows' reads, then their stores
-        long long wq[4];
-        float old[4];
-        float* cell[4];
+    // ---- rows due later: rounded once, added to the carried sums, cleared --
+    // (a wave takes four rows of 64 neurons, their reads before their stores,
+    // while the other blocks' lines arrive)
+    {
+      const int tiles = (nb + 63) >> 6, groups = (R + 3) >> 2;
+      int tile = __builtin_amdgcn_readfirstlane(wv), q0 = Dmin;
+      for (;;) {
+        while (tile >= tiles) {
+          tile -= tiles;
+          q0 += 4;
+        }
+        if (q0 >= Dmin + 4 * groups) break;
+        const int n = tile * 64 + lane;
+        int row = cb + q0, lr = lb + q0;
+        if constexpr (CL)
+          while (row >= crows) row -= crows;
+        if (lr >= a.L) lr -= a.L;
+        if (n < nb) {
+          long long wq[4];
+          float old[4];
+          float* cell[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int q = q0 + i < Dmax ? q0 + i : Dmax - 1;
-          wq[i] = win[q * B + tid];
-          cell[i] = CL ? carry + row * B + tid : a.rb + (int64_t)lr * N + gn;
-          old[i] = q < R ? *cell[i] : 0.f;
-          if (q0 + i + 1 < Dmax) {
-            if (++row == R) row = 0;
-            if (++lr == a.L) lr = 0;
+          for (int i = 0; i < 4; ++i) {
+            const int q = q0 + i < Dmax ? q0 + i : Dmax - 1;
+            wq[i] = win[q * B + n];
+            cell[i] = CL ? carry + row * B + n : a.rb + (int64_t)lr * N + j0 + n;
+            old[i] = q < R ? *cell[i] : 0.f;
+            if (q0 + i + 1 < Dmax) {
+              if (++row == crows) row = 0;
+              if (++lr == a.L) lr = 0;
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if (q0 + i >= Dmax) break;
+            win[(q0 + i) * B + n] = 0;
+            *cell[i] = old[i] + from_fixed(wq[i], inv);
           }
         }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (q0 + i >= Dmax) break;
-          win[(q0 + i) * B + tid] = 0;
-          *cell[i] = old[i] + from_fixed(wq[i], inv);
-        }
+        tile += nwv;
       }
     }
-    if (R > 0) {
+    if (crows > 0) {
       cb += Dmin;
-      while (cb >= R) cb -= R;
+      while (cb >= crows) cb -= crows;
     }
     lb += Dmin;
     if (lb >= a.L) lb -= a.L;
@@ -2390,7 +2466,7 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
       if (ok)
         for (int q = 0; q < R; ++q) {
           int row = cb + q, lr = lb + q;
-          if (row >= R) row -= R;
+          if (row >= crows) row -= crows;
           if (lr >= a.L) lr -= a.L;
           a.rb[(int64_t)lr * N + gn] = carry[row * B + tid];
         }
@@ -2657,6 +2733,8 @@ hipError_t launch_persist(hipStream_t s, const SliceArgs& a, uint32_t* const lis
   p.per_xcd = (a.NB + 7) / 8;
   p.cap = plan.cap;
   p.drows = plan.drows;
+  p.crows = plan.crows;
+  p.helpers = plan.helpers;
   p.epoch0 = epoch0;
   p.t0 = t0;
   p.rb_hi0 = rb_hi0;
