@@ -2460,6 +2460,7 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
     }
     cur ^= 1;
   }
+  __syncthreads();  // the last flush, by other waves than a neuron's own
   // ---- sums of the rows not yet due go to the HBM ring ---------------------
   if (own) {
     if constexpr (CL) {

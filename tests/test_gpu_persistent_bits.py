@@ -36,6 +36,10 @@ NETS = {
     "one_block": W.tiny(model=0, n=50, k=20, seed=5, d_lo=3, d_hi=7),
     "line_and_buffer": _busy(3000, d_lo=5, d_hi=9, d_min=5, d_max=9, block_neurons=128),
     "lds_list_full": _busy(4100, d_lo=6, d_hi=9, d_min=6, d_max=9, block_neurons=1024),
+    # 100 blocks of seven waves, some of whose columns another wave flushes
+    "wide_blocks": W.tiny(model=1, n=44_452, k=100, seed=7, d_lo=10, d_hi=20, block_neurons=448),
+    "wide_blocks_dmin1": W.tiny(model=1, n=44_452, k=100, seed=7, d_lo=1, d_hi=20,
+                                block_neurons=448),
     "ring_in_hbm": W.tiny(model=1, n=2400, k=200, seed=6, d_lo=10, d_hi=20, block_neurons=768),
 }
 
