@@ -138,19 +138,6 @@ struct SliceLauncher {
   int wform = 0;
 };
 
-// XCD-aware workgroup map: entry list[i] goes to workgroup
-// (i % per_xcd) * 8 + i / per_xcd, so consecutive entries share an XCD.
-std::vector<int2> xcd_map(const std::vector<int2>& list) {
-  const int64_t T = (int64_t)list.size();
-  const int64_t per_xcd = (T + 7) / 8;
-  std::vector<int2> map((size_t)(8 * per_xcd), make_int2(-1, 0));
-  for (int64_t gx = 0; gx < 8 * per_xcd; ++gx) {
-    const int64_t i = (gx & 7) * per_xcd + (gx >> 3);
-    if (i < T) map[(size_t)gx] = list[(size_t)i];
-  }
-  return map;
-}
-
 hipError_t launcher_init(SliceLauncher& L, int per, int cap, const std::vector<int2>& map,
                          size_t lds, int wform) {
   L.per = per;
@@ -347,6 +334,40 @@ struct sd_batch {
 };
 
 namespace {
+
+// XCD-aware workgroup map of several networks: entry k of XCD x goes to
+// workgroup 8 k + x.  Every network's blocks are dealt out evenly, a run of
+// consecutive ones to each XCD (they share segment lines in its L2), since
+// networks differ several times in work per block (in-degree and rate) and a
+// busy one kept on one XCD holds up the launch: 16 sweep nets took 320 us per
+// slice with whole networks per XCD, of which the other seven idled through
+// half.  Blocks that take more synapses per spike rate go first, so that the
+// last to start are short.
+std::vector<int2> xcd_map(const std::vector<sd_ctx*>& nets) {
+  std::vector<int32_t> order(nets.size());
+  for (size_t i = 0; i < nets.size(); ++i) order[i] = (int32_t)i;
+  auto weight = [&](int32_t i) { return (int64_t)nets[(size_t)i]->K * nets[(size_t)i]->B; };
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int32_t x, int32_t y) { return weight(x) > weight(y); });
+  std::vector<int2> per[8];
+  int64_t dealt = 0;  // blocks so far: where the next remainder goes
+  for (int32_t i : order) {
+    const int64_t NB = nets[(size_t)i]->NB;
+    int64_t b = 0;
+    for (int64_t k = 0; k < 8; ++k) {
+      const int64_t n = NB / 8 + (k < NB % 8 ? 1 : 0);
+      for (const int64_t e = b + n; b < e; ++b)
+        per[(dealt + k) % 8].push_back(make_int2(i, (int32_t)b));
+    }
+    dealt += NB;
+  }
+  size_t rows = 0;
+  for (const auto& p : per) rows = std::max(rows, p.size());
+  std::vector<int2> map(8 * rows, make_int2(-1, 0));
+  for (size_t x = 0; x < 8; ++x)
+    for (size_t k = 0; k < per[x].size(); ++k) map[8 * k + x] = per[x][k];
+  return map;
+}
 
 sd_status fail(sd_ctx* c, sd_status s, const char* fmt, ...) {
   if (c) {
@@ -2128,7 +2149,6 @@ sd_status sd_batch_create(const sd_config* cfgs, int32_t n, void* hip_stream, sd
     if (ci.plastic)
       return bfail(bt, SD_EUNSUPPORTED, "member " + std::to_string(i) + ": plastic synapses");
   }
-  std::vector<int2> blocks;
   size_t lds = 0;
   for (int32_t i = 0; i < n; ++i) {
     sd_ctx* c = nullptr;
@@ -2142,10 +2162,9 @@ sd_status sd_batch_create(const sd_config* cfgs, int32_t n, void* hip_stream, sd
     if (c->sm)
       return bfail(bt, SD_EUNSUPPORTED, "member " + std::to_string(i) +
                                             ": batches hold block-major networks only");
-    for (int32_t b = 0; b < c->NB; ++b) blocks.push_back(make_int2(i, b));
     lds = std::max(lds, slice_lds_bytes(c->B, cfgs[i].d_min, cfgs[i].d_max));
   }
-  const hipError_t e = launcher_init(bt->lau, n, 256, xcd_map(blocks), lds, c0.wform);
+  const hipError_t e = launcher_init(bt->lau, n, 256, xcd_map(bt->nets), lds, c0.wform);
   if (e != hipSuccess)
     return bfail(bt, SD_EHIP, std::string("launcher set-up failed: ") + hipGetErrorString(e));
   return SD_OK;
