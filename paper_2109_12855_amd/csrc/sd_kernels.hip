@@ -8,9 +8,8 @@
 //   block's ring window (d_max rows x B neurons, 64-bit fixed point), then
 //   advances its neurons through the next slice with the exact propagators
 //   (Sec. 2.1), reading inputs straight from the LDS window, and finally
-//   compacts the new spikes (each wave's ballot of a step kept as two mask
-//   words, then a block scan of their bit counts) and appends them, ordered
-//   (lag, neuron) within the block, to the slice's contiguous spike list.
+//   appends the new spikes, listed in LDS, to the slice's contiguous spike
+//   list.
 //   Rows of the window that are due in later slices are written to the ring
 //   in HBM by the threads without a neuron, during the update.
 //   Source-major layout: k_bin first sorts the slice's events by target
@@ -930,7 +929,7 @@ __host__ __device__ inline bool staged_in_regs(int B, int Dmin) {
 
 // LDS layout of a slice workgroup (byte offsets, 16-byte aligned pieces)
 struct SliceLds {
-  size_t win, carry, dcnt, mask, thr, scr, desc, meta, pm, pb, lagm, tpv, total;
+  size_t win, carry, dcnt, thr, scr, desc, meta, pm, pb, lagm, tpv, total;
 };
 __host__ __device__ inline SliceLds slice_lds_layout(int B, int Dmin, int win_rows,
                                                      bool plastic = false, bool bin = false) {
@@ -940,7 +939,7 @@ __host__ __device__ inline SliceLds slice_lds_layout(int B, int Dmin, int win_ro
   L.win = o;   o = up(o + (size_t)win_rows * B * 8);    // int64 ring window
   L.carry = o; o = up(o + (staged_in_regs(B, Dmin) ? 0 : (size_t)Dmin * B * 4));  // staged HBM rows
   L.dcnt = o;  o = up(o + (size_t)Dmin * B);            // Poisson-drive counts (u8)
-  L.mask = o;  o = up(o + (size_t)Dmin * (B / 32) * 4); // spike bitmask
+  o = up(o + (size_t)Dmin * (B / 32) * 4);  // spare: the block sizes that fit stay the same
   L.thr = o;   o = up(o + (size_t)kMaxThr * 4);         // drive thresholds
   L.scr = o;   o = up(o + (size_t)(kSliceThreads / 64 + 2) * 4);
   // one descriptor per spike of a chunk, plus one group of padding so a
@@ -1171,14 +1170,12 @@ __device__ __forceinline__ void slice_block(const SliceArgs& a, const int b) {
   const int B = a.B;
   const int64_t j0 = (int64_t)b * B;
   const int nb = (int)((a.N - j0) < B ? (a.N - j0) : B);
-  const int Wd = B >> 5;
   const int Dmin = a.Dmin;
 
   const SliceLds Lo = slice_lds_layout(B, Dmin, a.win_rows, PL, BIN);
   long long* win = (long long*)(lds_raw + Lo.win);
   float* carry = (float*)(lds_raw + Lo.carry);
   uint8_t* dcnt = lds_raw + Lo.dcnt;
-  uint32_t* mask = (uint32_t*)(lds_raw + Lo.mask);
   uint32_t* thr = (uint32_t*)(lds_raw + Lo.thr);
   int32_t* scr = (int32_t*)(lds_raw + Lo.scr);
   // spike c0 + i of the current chunk: its segment in this block (start
@@ -1187,6 +1184,9 @@ __device__ __forceinline__ void slice_block(const SliceArgs& a, const int b) {
   // back by whole waves as LDS broadcasts
   uint2* desc = (uint2*)(lds_raw + Lo.desc);
   uint32_t* meta = (uint32_t*)(lds_raw + Lo.meta);
+  // after the delivery the descriptors' place holds the block's new spikes
+  uint32_t* const slist = (uint32_t*)(lds_raw + Lo.desc);
+  constexpr int kSpkCap = (kSliceThreads + kMaxGroup) * 2;
   uint64_t* pm = (uint64_t*)(lds_raw + Lo.pm);
   int32_t* pb = (int32_t*)(lds_raw + Lo.pb);
   uint32_t* lagm = (uint32_t*)(lds_raw + Lo.lagm);
@@ -1225,17 +1225,18 @@ __device__ __forceinline__ void slice_block(const SliceArgs& a, const int b) {
   const int64_t w_lo = a.w_lo;
   if (a.do_deliver)
     for (int i = tid; i < a.Dmax * B; i += kSliceThreads) win[i] = 0;
-  for (int i = tid; i < Dmin * Wd; i += kSliceThreads) mask[i] = 0u;
   // events of this block, summed in LDS: one global atomic per workgroup
   // (thousands of same-address global atomics per launch back up the
   // memory queues of every compute unit)
   __shared__ unsigned long long s_ev;
   __shared__ long long s_zero;  // read by the update for steps outside the window
   __shared__ int s_fl;          // DYN: next neuron whose window rows go to the ring
+  __shared__ int s_spk;         // new spikes of the block
   if (tid == 0) {
     s_ev = 0;
     s_zero = 0;
     s_fl = 0;
+    s_spk = 0;
   }
   // the list counter of a later slice starts at zero
   if (b == 0 && tid == 0 && a.zero_cnt) *a.zero_cnt = 0;
@@ -1281,7 +1282,7 @@ __device__ __forceinline__ void slice_block(const SliceArgs& a, const int b) {
 
   // Poisson drive of the steps to update: one Philox4x64-10 block per
   // (neuron, 8-step chunk) gives eight 32-bit uniforms; the count is the
-  // number of CDF thresholds at or below each uniform.  Round k covers tasks
+  // number of CDF thresholds at or below each.  Round k covers tasks
   // k*1024 + tid; rounds are interleaved with the delivery loads below.
   int64_t c0 = 0;
   int n_tasks = 0;
@@ -1291,23 +1292,22 @@ __device__ __forceinline__ void slice_block(const SliceArgs& a, const int b) {
     n_tasks = (int)(c1 - c0 + 1) * nb;
   }
   const int n_rounds = (n_tasks + kSliceThreads - 1) / kSliceThreads;
+  const float inv_nb = 1.0f / (float)nb;
   auto drive_round = [&](int k) {
     const int task = k * kSliceThreads + tid;
     if (task >= n_tasks) return;
-    const int n = task % nb;
-    const int64_t c = c0 + task / nb;
+    // task / nb: the half keeps the FP32 quotient off the integers (tasks stay
+    // below 2^18)
+    const int ci = (int)(((float)task + 0.5f) * inv_nb);
+    const int n = task - ci * nb;
     uint64_t rr[4];
-    philox(a.seed, STREAM_DRIVE, (uint64_t)(j0 + n), (uint64_t)c, rr);
+    uint32_t cnt[8];
+    philox(a.seed, STREAM_DRIVE, (uint64_t)(j0 + n), (uint64_t)(c0 + ci), rr);
+    drive_counts(rr, thr, a.n_thr, cnt);
+    const int row = (int)((c0 + ci) * 8 - a.t_upd);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int64_t t = c * 8 + q;
-      if (t < a.t_upd || t >= a.t_upd + a.n_upd) continue;
-      const uint64_t word = rr[q >> 1];
-      const uint32_t u = (q & 1) ? (uint32_t)(word >> 32) : (uint32_t)word;
-      int cnt = 0;
-      while (cnt < a.n_thr && u >= thr[cnt]) ++cnt;  // thresholds ascend
-      dcnt[(int)(t - a.t_upd) * B + n] = (uint8_t)cnt;
-    }
+    for (int q = 0; q < 8; ++q)
+      if (row + q >= 0 && row + q < a.n_upd) dcnt[(row + q) * B + n] = (uint8_t)cnt[q];
   };
   int rounds_done = 0;
 
@@ -1518,7 +1518,7 @@ __device__ __forceinline__ void slice_block(const SliceArgs& a, const int b) {
   // keep the flush running long after the update.
   auto flush_rows = [&](int t0, int stride) {
     constexpr int kFl = 8;
-    const float inv = a.fx_inv;
+    const float inv = in_vgpr(a.fx_inv);
     int64_t t_first = a.t_upd + a.n_upd;
     if (t_first < w_lo) t_first = w_lo;
     const int nrows = (int)(w_lo + a.Dmax - t_first);
@@ -1562,9 +1562,10 @@ __device__ __forceinline__ void slice_block(const SliceArgs& a, const int b) {
   // on the (uniform) choice and waits for it there.
   auto update = [&](auto regs_tag) {
     constexpr bool kRegs = decltype(regs_tag)::value;
-    const float P11 = a.prop[0], P21 = a.prop[1], P22 = a.prop[2], P31 = a.prop[3];
-    const float P32 = a.prop[4], P33 = a.prop[5], P30Ie = a.prop[6], insc = a.prop[7];
-    const float inv = a.fx_inv;
+    const float P11 = in_vgpr(a.prop[0]), P21 = in_vgpr(a.prop[1]), P22 = in_vgpr(a.prop[2]);
+    const float P31 = in_vgpr(a.prop[3]), P32 = in_vgpr(a.prop[4]), P33 = in_vgpr(a.prop[5]);
+    const float P30Ie = in_vgpr(a.prop[6]), insc = in_vgpr(a.prop[7]);
+    const float inv = in_vgpr(a.fx_inv);
     for (int n = tid; n < nb; n += kSliceThreads) {
       const int64_t gn = j0 + n;
       float V, y1 = 0.f, y2 = 0.f;
@@ -1596,8 +1597,9 @@ __device__ __forceinline__ void slice_block(const SliceArgs& a, const int b) {
       // for the LDS reads issued before it: both share one counter)
       const int n_upd = a.n_upd, Dmax = a.Dmax;
       const bool deliv = a.do_deliver != 0;
-      const float drive_w = a.drive_w;
-      const float e_l = a.e_l, v_th = a.v_th, v_reset = a.v_reset;
+      const float drive_w = in_vgpr(a.drive_w), e_l = in_vgpr(a.e_l);
+      const float v_th = in_vgpr(a.v_th), v_reset = in_vgpr(a.v_reset);
+      uint32_t fired = 0;  // bit s: a spike in step s of the update (n_upd <= 31)
       const int ref_steps = a.ref_steps, lag_upd = (int)(a.t_upd - a.t_slice0);
       const bool delta = a.model == MODEL_DELTA;
       for (int s0 = 0; s0 < n_upd; s0 += kSteps) {
@@ -1658,16 +1660,31 @@ __device__ __forceinline__ void slice_block(const SliceArgs& a, const int b) {
           if (hm >> 63) hb = (int32_t)(a.t_upd + s) - 64;
           hm = (hm << 1) | (uint64_t)spk;
         }
-        {
-          // the step's spikes of this wave's 64 neurons (consecutive, first
-          // lane active whenever any is): one ballot, two mask words
-          const uint64_t bal = __ballot(spk);
-          if (lane == 0) {
-            const int w0 = (n - lane) >> 5;
-            mask[(lag_upd + s) * Wd + w0] = (uint32_t)bal;
-            mask[(lag_upd + s) * Wd + w0 + 1] = (uint32_t)(bal >> 32);
-          }
+        fired |= (uint32_t)spk << s;
         }
+      }
+      // new spikes, rare: into the block's LDS list, any order (past its end
+      // straight to the slice's list)
+      while (fired) {
+        const int s = __ffs(fired) - 1;
+        fired &= fired - 1;
+        const uint32_t ent = ((uint32_t)gn << 5) | (uint32_t)(lag_upd + s);
+        const int at =
+            __hip_atomic_fetch_add(&s_spk, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (at < kSpkCap) {
+          slist[at] = ent;
+          continue;
+        }
+        if (!PL && a.write_list) {
+          const int64_t pos = atomicAdd(a.out_cnt, 1);
+          if (pos < a.out_cap) a.out_list[pos] = ent;
+          else atomicOr(a.overflow, 1);
+        }
+        if (a.rec) {
+          const unsigned long long rp = atomicAdd(a.rec_n, 1ull);
+          if ((int64_t)rp < a.rec_cap)
+            a.rec[rp] = make_uint2((uint32_t)(a.t_slice0 + lag_upd + s), (uint32_t)gn);
+          else atomicOr(a.overflow, 2);
         }
       }
       if constexpr (PL) {
@@ -1741,54 +1758,35 @@ __device__ __forceinline__ void slice_block(const SliceArgs& a, const int b) {
     }
   }
 
-  // ---- compaction: this block's new spikes, (lag, neuron) ordered --------
+  // ---- compaction: the block's new spikes to the slice's list and raster ---
   // (plastic nets: their list entries are built above; here the raster and
-  // the spike count only)
+  // the spike count only).  One reservation per block and list.
   if (a.n_upd > 0) {
-    const int write_list = PL ? 0 : a.write_list;
-    const int lag0 = (int)(a.t_upd - a.t_slice0);
-    const int nq = a.n_upd * Wd;
-    __shared__ int s_base;
-    __shared__ unsigned long long s_rbase;
-    int running = 0;
-    for (int q0 = 0; q0 < nq; q0 += kSliceThreads) {
-      const int q = q0 + tid;
-      uint32_t m = (q < nq) ? mask[lag0 * Wd + q] : 0u;
-      int tot;
-      const int ex = block_excl_scan<int>(__popc(m), scr, tot);
-      if (tot == 0) continue;
-      // one reservation per block in the slice's list (and the raster)
+    const int n_spk = s_spk, n_lds = n_spk < kSpkCap ? n_spk : kSpkCap;
+    if (n_spk > 0) {
+      __shared__ int s_base;
+      __shared__ unsigned long long s_rbase;
+      const bool write_list = !PL && a.write_list;
       if (tid == 0) {
-        s_base = write_list ? atomicAdd(a.out_cnt, tot) : 0;
-        s_rbase = a.rec ? atomicAdd(a.rec_n, (unsigned long long)tot) : 0ull;
+        s_base = write_list ? atomicAdd(a.out_cnt, n_lds) : 0;
+        s_rbase = a.rec ? atomicAdd(a.rec_n, (unsigned long long)n_lds) : 0ull;
+        atomicAdd(a.spk_count, (unsigned long long)n_spk);
       }
       __syncthreads();
-      const int64_t base = s_base;
-      const unsigned long long rbase = s_rbase;
-      __syncthreads();
-      int pos = ex;
-      const int lg = lag0 + q / Wd;
-      const int nbase = (q % Wd) * 32;
-      while (m) {
-        const int bit = __ffs(m) - 1;
-        m &= m - 1;
-        const int64_t gn = j0 + nbase + bit;
+      for (int i = tid; i < n_lds; i += kSliceThreads) {
+        const uint32_t ent = slist[i];
         if (write_list) {
-          if (base + pos < a.out_cap)
-            a.out_list[base + pos] = ((uint32_t)gn << 5) | (uint32_t)lg;
-          else
-            atomicOr(a.overflow, 1);
+          if ((int64_t)s_base + i < a.out_cap) a.out_list[s_base + i] = ent;
+          else atomicOr(a.overflow, 1);
         }
         if (a.rec) {
-          const unsigned long long rp = rbase + (unsigned long long)pos;
-          if ((int64_t)rp < a.rec_cap) a.rec[rp] = make_uint2((uint32_t)(a.t_slice0 + lg), (uint32_t)gn);
+          const unsigned long long rp = s_rbase + (unsigned long long)i;
+          if ((int64_t)rp < a.rec_cap)
+            a.rec[rp] = make_uint2((uint32_t)(a.t_slice0 + (ent & 31u)), ent >> 5);
           else atomicOr(a.overflow, 2);
         }
-        ++pos;
       }
-      running += tot;
     }
-    if (tid == 0 && running) atomicAdd(a.spk_count, (unsigned long long)running);
   }
 }
 
