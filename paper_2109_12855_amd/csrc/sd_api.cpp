@@ -780,6 +780,18 @@ sd_status launch_slice_checked(sd_ctx* c, const SliceArgs& a) {
   return SD_OK;
 }
 
+// Lanes per segment of the block-major walk: the fewest that hold a segment of
+// mean length m = K B / N and two standard deviations (Poisson) more; with 64,
+// a segment of 6 to 22 synapses leaves most of a wave idle.  20 slices of
+// 30,011 neurons (m = 12.8): 304 us with 64 lanes, 252 with 32, 273 with 16,
+// where a fifth of the segments take a second round; 100 slices of 1,250
+// neurons (m = 6.4): 768 us with 64, 674 with 16.
+int32_t walk_lanes(const sd_ctx* c) {
+  const double m = (double)c->K * c->B / (double)c->N;
+  const double top = m + 2.0 * std::sqrt(m);
+  return top <= 16.0 ? 16 : top <= 32.0 ? 32 : 64;
+}
+
 SliceArgs base_args(sd_ctx* c) {
   SliceArgs a;
   std::memset(&a, 0, sizeof a);
@@ -788,6 +800,7 @@ SliceArgs base_args(sd_ctx* c) {
   a.n_src = c->n_src;
   a.syn = c->syn;
   a.K = c->K;
+  a.seg_lanes = walk_lanes(c);
   a.N = c->N;
   a.NB = c->NB;
   a.B = c->B;

@@ -43,6 +43,7 @@ struct SliceArgs {
   int64_t N;               // local neurons
   int32_t NB, B;           // blocks, neurons per block
   int32_t K;               // in-degree: block b's synapses start at b * B * K
+  int32_t seg_lanes;       // lanes per segment of the block-major walk (16, 32, 64)
   int32_t Dmin, Dmax, L;
   int32_t win_rows;        // rows of the LDS window (Dmax; 0: no LDS delivery)
   int64_t src_e_end;       // source ids below this are excitatory

@@ -1072,6 +1072,72 @@ __device__ __forceinline__ void walk_chunk(const SliceArgs& a, const uint2* desc
   }
 }
 
+// The walk for short segments: LPS lanes (16 or 32) per segment, so a slot of
+// the wave takes 64 / LPS of them.  A segment's place, count and meta word are
+// then per lane.  Segments longer than LPS take further rounds.
+template <int KF, int LPS, typename F>
+__device__ __forceinline__ void walk_short(const SliceArgs& a, const uint2* desc,
+                                           const uint32_t* meta, int n_c, int* s_next,
+                                           long long* win, int lane, F in_flight) {
+  constexpr int SPS = 64 / LPS;        // segments per slot
+  constexpr int G = LPS == 16 ? 4 : 6; // slots per group
+  const float m0e = in_vgpr(a.wm0_e), m0i = in_vgpr(a.wm0_i);
+  const float m1e = in_vgpr(a.wm1_e), m1i = in_vgpr(a.wm1_i);
+  const int sub = lane / LPS, sl = lane & (LPS - 1);
+  auto add = [&](const SynRaw<KF>& x, uint32_t m) {
+    const bool inh = (int32_t)m < 0;
+    int slot, v;
+    syn_decode<KF>(x, inh ? m0i : m0e, inh ? m1i : m1e, slot, v);
+    __hip_atomic_fetch_add((unsigned long long*)&win[(int)((m >> 7) & 0xffffffu) + slot],
+                           (unsigned long long)(long long)v, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  for (;;) {
+    int g0 = 0;
+    if (lane == 0)
+      g0 = __hip_atomic_fetch_add(s_next, G * SPS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    g0 = __builtin_amdgcn_readfirstlane(g0);
+    if (g0 >= n_c) break;
+    SynRaw<KF> raw[G];
+    uint32_t mt[G];
+    int cnt[G];
+    bool any_long = false;
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const int i = g0 + u * SPS + sub;  // past the chunk: stale or padding, masked
+      const uint2 d = desc[i];
+      mt[u] = meta[i];
+      cnt[u] = i < n_c ? (int)d.y : 0;
+      raw[u] = syn_fetch<KF>(a.syn, sl < cnt[u] ? d.x + (uint32_t)sl : 0u);
+      any_long |= cnt[u] > LPS;
+    }
+    in_flight();
+#pragma unroll
+    for (int u = 0; u < G; ++u)
+      if (sl < cnt[u]) add(raw[u], mt[u]);
+    if (__any(any_long)) {
+#pragma unroll 1
+      for (int u = 0; u < G; ++u) {
+        const int i = g0 + u * SPS + sub;
+        const uint2 d = desc[i];
+        const uint32_t m = meta[i];
+        const int n = i < n_c ? (int)d.y : 0;
+        for (int e = LPS + sl; __any(e < n); e += LPS)
+          if (e < n) add(syn_fetch<KF>(a.syn, d.x + (uint32_t)e), m);
+      }
+    }
+  }
+}
+
+template <int KF, typename F>
+__device__ __forceinline__ void walk_any(int lps, const SliceArgs& a, const uint2* desc,
+                                         const uint32_t* meta, int n_c, int* s_next,
+                                         long long* win, int lane, F in_flight) {
+  if (lps == 64) walk_chunk<KF>(a, desc, meta, n_c, s_next, win, lane, in_flight);
+  else if (lps == 32) walk_short<KF, 32>(a, desc, meta, n_c, s_next, win, lane, in_flight);
+  else walk_short<KF, 16>(a, desc, meta, n_c, s_next, win, lane, in_flight);
+}
+
 // The same walk for a plastic net: each lane's synapse takes the entry's
 // spikes in lag order (static inhibitory ones only add), its weight updated
 // before each add and stored back.
@@ -1460,7 +1526,7 @@ __device__ __forceinline__ void slice_block(const SliceArgs& a, const int b) {
         walk_plastic(a, desc, meta, lagm, tpv, pm, pb, n_c, &s_next, win, w_lo, Dmin, B, lane,
                      drive_next);
       else
-        walk_chunk<KF>(a, desc, meta, n_c, &s_next, win, lane, drive_next);
+        walk_any<KF>(a.seg_lanes, a, desc, meta, n_c, &s_next, win, lane, drive_next);
       __syncthreads();  // the next chunk overwrites the descriptors
     }
     if (total == 0) {  // no chunk stored the thresholds or made the zeroing visible
@@ -2240,7 +2306,7 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
         total = s_tot;
       }
       const int n_c = (int)(total - c0 < CAP ? total - c0 : CAP);
-      walk_chunk<KF>(a, desc, meta, n_c, &s_next, win, lane, [] {});
+      walk_any<KF>(a.seg_lanes, a, desc, meta, n_c, &s_next, win, lane, [] {});
       __syncthreads();  // window adds and drive counts complete
       if (c0 + CAP >= total) break;
     }
