@@ -971,10 +971,13 @@ size_t slice_lds_bytes(int B, int Dmin, int win_rows, bool plastic, bool bin) {
 // then added into the window row of its arrival step.  T is the first step
 // after the masks (the window's first step): bit k of pm is step T - 1 - k.
 // The arrival row of lag l is l + d - Dmin.
-__device__ __forceinline__ float plastic_walk(const SliceArgs& a, float w, int d, uint64_t pm,
+struct PairRule {  // the rule's constants and the weights' fixed-point scales
+  float ap, am, kp, km, wmax, m1e, m1i;
+};
+__device__ __forceinline__ float plastic_walk(const PairRule& s, float w, int d, uint64_t pm,
                                               int32_t pb, uint32_t lm, int32_t tprev, int32_t t0,
-                                              int32_t T, int Dmin, int B, int jl, long long* win,
-                                              float m1) {
+                                              int32_t T, int Dmin, int B, int jl,
+                                              long long* win) {
   while (lm) {
     const int l = __ffs(lm) - 1;
     lm &= lm - 1;
@@ -985,13 +988,13 @@ __device__ __forceinline__ float plastic_walk(const SliceArgs& a, float w, int d
     const int32_t t_last = mk ? c - (int32_t)__builtin_ctzll(mk) : pb;
     if (t_last >= 0) {
       if (tprev >= 0 && t_last + d > tprev) {
-        w += a.stdp_ap * exp2f(-(float)(t_last + d - tprev) * a.stdp_kp);
-        w = fminf(w, a.stdp_wmax);
+        w += s.ap * exp2f(-(float)(t_last + d - tprev) * s.kp);
+        w = fminf(w, s.wmax);
       }
-      w -= a.stdp_am * exp2f(-(float)(t_pre - t_last - d) * a.stdp_km);
+      w -= s.am * exp2f(-(float)(t_pre - t_last - d) * s.km);
       w = fmaxf(w, 0.f);
     }
-    const int v = (int)(m1 * w);          // conversion truncates toward zero
+    const int v = (int)(s.m1e * w);       // conversion truncates toward zero
     __hip_atomic_fetch_add((unsigned long long*)&win[(l + d - Dmin) * B + jl],
                            (unsigned long long)(long long)v, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1141,14 +1144,14 @@ __device__ __forceinline__ void walk_any(int lps, const SliceArgs& a, const uint
 // The same walk for a plastic net: each lane's synapse takes the entry's
 // spikes in lag order (static inhibitory ones only add), its weight updated
 // before each add and stored back.
-__device__ __forceinline__ void plastic_synapse(const SliceArgs& a, uint2 r, uint32_t at, bool inh,
-                                                uint32_t lm, int32_t tprev, const uint64_t* pm,
-                                                const int32_t* pb, long long* win, int64_t w_lo,
-                                                int Dmin, int B) {
+__device__ __forceinline__ void plastic_synapse(const SliceArgs& a, const PairRule& rule, uint2 r,
+                                                uint32_t at, bool inh, uint32_t lm, int32_t tprev,
+                                                uint64_t pm, int32_t pb, long long* win,
+                                                int64_t w_lo, int Dmin, int B) {
   float w = __uint_as_float(r.x);
   const int slot = (int)(r.y & ((1u << kSynSlotBits) - 1u));
   if (inh) {
-    const int v = (int)(a.wm1_i * w);
+    const int v = (int)(rule.m1i * w);
     while (lm) {
       const int l = __ffs(lm) - 1;
       lm &= lm - 1;
@@ -1158,8 +1161,8 @@ __device__ __forceinline__ void plastic_synapse(const SliceArgs& a, uint2 r, uin
     }
   } else {
     const int q = (int)(r.y >> kSynSlotBits), jl = slot - q * B;
-    w = plastic_walk(a, w, Dmin + q, pm[jl], pb[jl], lm, tprev, (int32_t)(w_lo - Dmin),
-                     (int32_t)w_lo, Dmin, B, jl, win, a.wm1_e);
+    w = plastic_walk(rule, w, Dmin + q, pm, pb, lm, tprev, (int32_t)(w_lo - Dmin), (int32_t)w_lo,
+                     Dmin, B, jl, win);
     ((uint32_t*)a.syn)[2 * (size_t)at] = __float_as_uint(w);
   }
 }
@@ -1172,6 +1175,11 @@ __device__ __forceinline__ void walk_plastic(const SliceArgs& a, const uint2* de
                                              long long* win, int64_t w_lo, int Dmin, int B,
                                              int lane, F in_flight) {
   constexpr int G = SynGroup<KF_F32>::n;
+  // read per synapse from the arguments, each constant costs a scalar load and
+  // a wait that the LDS adds before it share
+  const PairRule rule = {in_vgpr(a.stdp_ap),   in_vgpr(a.stdp_am), in_vgpr(a.stdp_kp),
+                         in_vgpr(a.stdp_km),   in_vgpr(a.stdp_wmax), in_vgpr(a.wm1_e),
+                         in_vgpr(a.wm1_i)};
   for (;;) {
     int g0 = 0;
     if (lane == 0)
@@ -1194,6 +1202,19 @@ __device__ __forceinline__ void walk_plastic(const SliceArgs& a, const uint2* de
       mt[u] = meta[g0 + u];
       any_long |= (mt[u] & 127u) > 64u;
     }
+    // the targets' spike histories of the whole group, then the updates: read
+    // by each synapse in its turn they are an LDS round trip per slot
+    uint64_t hm[G];
+    int32_t hb[G];
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const int slot = (int)(raw[u].r.y & ((1u << kSynSlotBits) - 1u));
+      const int q = (int)(raw[u].r.y >> kSynSlotBits), jl = slot - q * B;
+      const int at = (u < n_here && lane < (int)(mt[u] & 127u)) ? jl : 0;
+      hm[u] = pm[at];
+      hb[u] = pb[at];
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < G; ++u) {
       const uint32_t m = __builtin_amdgcn_readfirstlane(mt[u]);
@@ -1201,8 +1222,8 @@ __device__ __forceinline__ void walk_plastic(const SliceArgs& a, const uint2* de
       const int32_t tp0 = __builtin_amdgcn_readfirstlane(tpv[g0 + u]);
       const uint32_t sx = __builtin_amdgcn_readfirstlane(desc[g0 + u].x);
       if ((u < n_here) & (lane < (int)(m & 127u)) & (lane < 64))
-        plastic_synapse(a, raw[u].r, sx + (uint32_t)lane, (int32_t)m < 0, lm, tp0, pm, pb, win,
-                        w_lo, Dmin, B);
+        plastic_synapse(a, rule, raw[u].r, sx + (uint32_t)lane, (int32_t)m < 0, lm, tp0, hm[u], hb[u],
+                        win, w_lo, Dmin, B);
     }
     // segments longer than one wave
     if (__builtin_amdgcn_readfirstlane((int)any_long)) {
@@ -1213,8 +1234,10 @@ __device__ __forceinline__ void walk_plastic(const SliceArgs& a, const uint2* de
         for (int e0 = 64; e0 < sl; e0 += 64) {
           if (lane + e0 >= sl) continue;
           const uint32_t at = d.x + (uint32_t)(e0 + lane);
-          plastic_synapse(a, syn_fetch<KF_F32>(a.syn, at).r, at, (int32_t)m < 0, lagm[g0 + u],
-                          tpv[g0 + u], pm, pb, win, w_lo, Dmin, B);
+          const uint2 r = syn_fetch<KF_F32>(a.syn, at).r;
+          const int jl = (int)(r.y & ((1u << kSynSlotBits) - 1u)) - (int)(r.y >> kSynSlotBits) * B;
+          plastic_synapse(a, rule, r, at, (int32_t)m < 0, lagm[g0 + u], tpv[g0 + u], pm[jl], pb[jl], win,
+                          w_lo, Dmin, B);
         }
       }
     }
