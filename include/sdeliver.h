@@ -204,8 +204,9 @@ sd_status sd_update_neurons(sd_ctx* ctx, int32_t n_steps);
  * every synapse (src -> j, delay d, weight w): ring[t0 + lag + d][j] += w.
  * d_src/d_lag: n device entries (u32 source ids, u8 lags), borrowed until the
  * stream reaches the call; n == 0: nothing to add.  0 <= n <= n_blocks *
- * block_neurons * d_min (the context's list capacity), else SD_EINVAL.  The list is packed
- * and validated on the device into the context's own buffer (no host round
+ * block_neurons * d_min (the context's list capacity; source-major with an
+ * automatic block size: of the largest block size that fits), else SD_EINVAL.
+ * The list is packed and validated on the device into the context's own buffer (no host round
  * trip, no allocation): an entry with src >= n_src or lag >= d_min delivers
  * nothing and sets a sticky flag that the next sd_get_stats reports as
  * SD_EINVAL (bit 3 of sd_stats.overflow).  The window [t0 + d_min,
