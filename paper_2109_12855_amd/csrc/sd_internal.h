@@ -28,7 +28,10 @@ constexpr int kFillChunk = 2048;     // draws ranked per build iteration
 //   WF_BF16        u32: low half BF16 weight, high half the slot
 //   WF_BF16_RESID  u32: low half BF16 residual d (w = mu (1 + d)), high half
 //   and WF_PACKED  the slot
-// All forms but the packed one also keep a u8 delay array (exports).
+// All forms but the packed one also keep a u8 delay array (exports).  A record
+// of target and delay took a second load and a multiply-add per synapse: 20
+// slices of the 112,500-neuron net in FP32 660 -> 619 us, 14 of 16 sweep nets
+// 5640 -> 5092 us.
 constexpr int kSynSlotBits = 16;
 // kernel forms: records of 8 bytes, or of 4 (the BF16 forms differ in their
 // fixed-point constants only)

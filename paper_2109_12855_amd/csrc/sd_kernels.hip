@@ -886,7 +886,10 @@ __device__ __forceinline__ float from_fixed(long long q, float inv) {
 // to kMaxThr with 2^32 - 1) is read four thresholds at a time, one broadcast
 // for all eight uniforms, until no lane's largest uniform reaches further: a
 // uniform searched by itself waits for an LDS read per threshold.  A uniform
-// of 2^32 - 1 counts padding too, hence the bound.
+// of 2^32 - 1 counts padding too, hence the bound.  With the new spikes listed
+// in LDS rather than balloted and scanned per step: 50 slices of the
+// 1,125,000-neuron share 30.3 -> 29.0 ms, 14 of 16 sweep nets 3147 -> 2980 us,
+// 20 plastic ones of 112,500 neurons 1271 -> 1152 us.
 __device__ __forceinline__ void drive_counts(const uint64_t rr[4], const uint32_t* thr, int n_thr,
                                              uint32_t cnt[8]) {
   uint32_t u[8], top = 0u;
@@ -1077,7 +1080,10 @@ __device__ __forceinline__ void walk_chunk(const SliceArgs& a, const uint2* desc
 
 // The walk for short segments: LPS lanes (16 or 32) per segment, so a slot of
 // the wave takes 64 / LPS of them.  A segment's place, count and meta word are
-// then per lane.  Segments longer than LPS take further rounds.
+// then per lane.  Segments longer than LPS take further rounds.  What bounds a
+// small net's walk is the loads in flight per wave and the instructions per
+// segment, not the bytes: 14 slices of 16 nets of the sweep took 2980 us with
+// a wave per segment and take 2553 this way.
 template <int KF, int LPS, typename F>
 __device__ __forceinline__ void walk_short(const SliceArgs& a, const uint2* desc,
                                            const uint32_t* meta, int n_c, int* s_next,
@@ -1143,7 +1149,11 @@ __device__ __forceinline__ void walk_any(int lps, const SliceArgs& a, const uint
 
 // The same walk for a plastic net: each lane's synapse takes the entry's
 // spikes in lag order (static inhibitory ones only add), its weight updated
-// before each add and stored back.
+// before each add and stored back.  Bound by the rule's vector instructions
+// (two exponentials per spike): 20 slices of the 112,500-neuron net took 1160
+// us with the rule's constants read from the arguments per synapse and the
+// histories one slot at a time, 1098 with both read per group (1140 with
+// groups of 6).
 __device__ __forceinline__ void plastic_synapse(const SliceArgs& a, const PairRule& rule, uint2 r,
                                                 uint32_t at, bool inh, uint32_t lm, int32_t tprev,
                                                 uint64_t pm, int32_t pb, long long* win,
@@ -1959,8 +1969,8 @@ __global__ void __launch_bounds__(kSliceThreads) k_slice1(SingleArgs s) {
 // block's part of the slice's list buffer, between a release and an acquire
 // fence.
 // Per slice, one launch per slice against this kernel (stretches of 20 to 100
-// slices): 1,250-neuron delta net 14.9 -> 7.4 us, 30,011 alpha neurons 22.5 ->
-// 13, 112,500 packed 32.8 -> 22, FP32 37.6 -> 25, one-step slices 20.5 -> 8.7.
+// slices): 1,250-neuron delta net 14.9 -> 6.7 us, 30,011 alpha neurons 22.5 ->
+// 11, 112,500 packed 32.8 -> 22, FP32 37.6 -> 25, one-step slices 20.5 -> 8.7.
 // Three polls in flight instead of one were 2% slower, spike groups split
 // evenly over the waves 1-3%.
 constexpr int64_t kBarSpin = 1LL << 22;  // polls before a wait gives up (explicit mode)
