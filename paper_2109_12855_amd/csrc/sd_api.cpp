@@ -246,7 +246,6 @@ struct sd_ctx {
   uint32_t* tile_sums = nullptr;
   int64_t n_tiles = 0;
   void* syn = nullptr;          // synapse records
-  uint8_t* syn_dly = nullptr;   // delays (not used by the packed form)
   float *V = nullptr, *y1 = nullptr, *y2 = nullptr;
   int32_t* r = nullptr;
   float* rb = nullptr;
@@ -758,7 +757,10 @@ sd_status make_layout(const sd_config* c, Layout* L, std::string* why) {
   L->off_cursor = take((size_t)L->M * ptr);
   L->off_seg = take(L->sm ? 0 : (size_t)L->n_src * L->NB * 8);
   L->off_tiles = take((size_t)L->n_tiles * ptr);
-  L->off_syn = take(std::max<size_t>((size_t)L->n_syn * L->rec_bytes, 16));  // record 0 always readable
+  // record 0 always readable; the FP32 form fills 6 of its 8 bytes per synapse,
+  // and no block-major form the byte of a delay (every slot holds it): the sizes
+  // that callers see stay as they are
+  L->off_syn = take(std::max<size_t>((size_t)L->n_syn * L->rec_bytes, 16));
   L->off_dly = take(std::max<size_t>((size_t)L->n_syn * L->dly_bytes, 16));
   L->off_V = take((size_t)L->N * 4);
   L->off_y1 = take((size_t)L->N * 4);
@@ -825,6 +827,11 @@ int32_t walk_lanes(const sd_ctx* c) {
   const double m = (double)c->K * c->B / (double)c->N;
   const double top = m + 2.0 * std::sqrt(m);
   return top <= 16.0 ? 16 : top <= 32.0 ? 32 : 64;
+}
+
+// Window slots of the FP32 block-major table, after its weights.
+uint16_t* fp32_slots(const sd_ctx* c) {
+  return c->sm || c->cfg.wform != SD_W_FP32 ? nullptr : (uint16_t*)((float*)c->syn + c->n_syn);
 }
 
 SliceArgs base_args(sd_ctx* c) {
@@ -898,6 +905,7 @@ SliceArgs base_args(sd_ctx* c) {
   if (g.plastic) {
     const double ln2 = std::log(2.0);
     a.plastic = 1;
+    a.rows_inv = 0xffffffffu / (uint32_t)c->B + 1u;
     a.pmask = c->pmask;
     a.pbefore = c->pbefore;
     a.stdp_ap = (float)g.stdp_a_plus;
@@ -961,7 +969,7 @@ sd_status bin_events(sd_ctx* c, const uint32_t* in_list, const int32_t* in_cnt, 
 }
 
 // Decode record e of a host copy of the synapse arrays (b: its block).
-void decode_record(const sd_config& g, const uint8_t* rec, const uint8_t* dl, uint32_t e,
+void decode_record(const sd_config& g, const uint8_t* rec, uint32_t e,
                    int32_t b, int32_t B, float mu, int32_t* tgt, float* w, uint8_t* dly) {
   uint32_t slot;
   if (g.wform == SD_W_FP32) {
@@ -981,7 +989,7 @@ void decode_record(const sd_config& g, const uint8_t* rec, const uint8_t* dl, ui
   }
   // slot = (delay - d_min) * B + offset
   *tgt = (int32_t)((int64_t)b * B + (int32_t)(slot % (uint32_t)B));
-  *dly = g.wform == SD_W_BF16_PACKED ? (uint8_t)(g.d_min + (int)(slot / (uint32_t)B)) : dl[e];
+  *dly = (uint8_t)(g.d_min + (int)(slot / (uint32_t)B));
 }
 
 // Point the delivery arguments at the completed slice's spikes: the
@@ -1069,7 +1077,6 @@ sd_status sd_create(const sd_config* cfg, void* hip_stream, void* d_arena, size_
   c->seg = (uint2*)(A + L.off_seg);
   c->tile_sums = (uint32_t*)(A + L.off_tiles);
   c->syn = A + L.off_syn;
-  c->syn_dly = (uint8_t*)(A + L.off_dly);
   c->V = (float*)(A + L.off_V);
   c->y1 = (float*)(A + L.off_y1);
   c->y2 = (float*)(A + L.off_y2);
@@ -1094,7 +1101,6 @@ sd_status sd_create(const sd_config* cfg, void* hip_stream, void* d_arena, size_
     c->cursor = nullptr;
     c->seg = nullptr;
     c->syn = nullptr;
-    c->syn_dly = nullptr;
   }
   c->rb = (float*)(A + L.off_rb);
   c->list[0] = (uint32_t*)(A + L.off_list0);
@@ -1241,7 +1247,7 @@ sd_status sd_build_connections(sd_ctx* c) {
   a.cursor = c->cursor;
   a.seg = c->seg;
   a.syn = c->syn;
-  a.syn_dly = c->syn_dly;
+  a.slots = fp32_slots(c);
   a.wform = g.wform;
   a.d_min = g.d_min;
   a.wtab_e = c->wtab_e;
@@ -2037,11 +2043,21 @@ sd_status sd_export_connections(sd_ctx* c, int64_t* h_row, int32_t* h_tgt, uint8
   if (!h_tgt && !h_dly && !h_w) return SD_OK;
   const sd_config& g = c->cfg;
   const int rb = g.wform == SD_W_FP32 ? 8 : 4;
-  std::vector<uint8_t> rec((size_t)c->n_syn * rb), dl((size_t)c->n_syn);
+  std::vector<uint8_t> rec((size_t)c->n_syn * rb);
   if (c->n_syn) {
-    HIP_TRY(c, hipMemcpy(rec.data(), c->syn, rec.size(), hipMemcpyDeviceToHost));
-    if (g.wform != SD_W_BF16_PACKED)
-      HIP_TRY(c, hipMemcpy(dl.data(), c->syn_dly, dl.size(), hipMemcpyDeviceToHost));
+    const size_t n = (size_t)c->n_syn;
+    if (const uint16_t* slots = fp32_slots(c)) {  // weights and slots to records
+      std::vector<uint32_t> w(n);
+      std::vector<uint16_t> sl(n);
+      HIP_TRY(c, hipMemcpy(w.data(), c->syn, n * 4, hipMemcpyDeviceToHost));
+      HIP_TRY(c, hipMemcpy(sl.data(), slots, n * 2, hipMemcpyDeviceToHost));
+      for (size_t i = 0; i < n; ++i) {
+        const uint64_t r = (uint64_t)sl[i] << 32 | w[i];
+        std::memcpy(rec.data() + i * 8, &r, 8);
+      }
+    } else {
+      HIP_TRY(c, hipMemcpy(rec.data(), c->syn, rec.size(), hipMemcpyDeviceToHost));
+    }
   }
   for (int64_t s = 0; s < S; ++s) {
     int64_t at = h_row[s];
@@ -2051,7 +2067,7 @@ sd_status sd_export_connections(sd_ctx* c, int64_t* h_row, int32_t* h_tgt, uint8
         int32_t t;
         float w;
         uint8_t d;
-        decode_record(g, rec.data(), dl.data(), e, b, c->B, mu, &t, &w, &d);
+        decode_record(g, rec.data(), e, b, c->B, mu, &t, &w, &d);
         if (h_tgt) h_tgt[at] = t;
         if (h_w) h_w[at] = w;
         if (h_dly) h_dly[at] = d;
@@ -2128,29 +2144,24 @@ sd_status sd_export_block(sd_ctx* c, int32_t b, int64_t* h_row, int32_t* h_tgt, 
   if (!h_tgt || tot == 0) return SD_OK;
   const sd_config& g = c->cfg;
   const int rb = g.wform == SD_W_FP32 ? 8 : 4;
-  const bool has_dly = g.wform != SD_W_BF16_PACKED;
   // gather the block's segments source by source on the device
   int64_t* d_off = nullptr;
   char* d_out = nullptr;
   hipError_t e = hipMalloc((void**)&d_off, (size_t)S * 8);
-  if (e == hipSuccess) e = hipMalloc((void**)&d_out, (size_t)tot * (rb + 1));
+  if (e == hipSuccess) e = hipMalloc((void**)&d_out, (size_t)tot * rb);
   if (e == hipSuccess) e = hipMemcpy(d_off, h_row, (size_t)S * 8, hipMemcpyHostToDevice);
   if (e == hipSuccess)
-    e = launch_gather_block(c->stream, c->seg, S, c->NB, b, d_off, c->syn,
-                            has_dly ? c->syn_dly : nullptr, rb, d_out,
-                            has_dly ? (uint8_t*)(d_out + (size_t)tot * rb) : nullptr);
-  std::vector<uint8_t> rec((size_t)tot * rb), dl((size_t)tot);
+    e = launch_gather_block(c->stream, c->seg, S, c->NB, b, d_off, c->syn, fp32_slots(c), d_out);
+  std::vector<uint8_t> rec((size_t)tot * rb);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e == hipSuccess) e = hipMemcpy(rec.data(), d_out, rec.size(), hipMemcpyDeviceToHost);
-  if (e == hipSuccess && has_dly)
-    e = hipMemcpy(dl.data(), d_out + (size_t)tot * rb, dl.size(), hipMemcpyDeviceToHost);
   if (d_off) (void)hipFree(d_off);
   if (d_out) (void)hipFree(d_out);
   if (e != hipSuccess) return fail(c, SD_EHIP, "block export failed: %s", hipGetErrorString(e));
   for (int64_t s = 0; s < S; ++s) {
     const float mu = s < c->src_e_end ? c->mu_e : c->mu_i;
     for (int64_t k = h_row[s]; k < h_row[s + 1]; ++k)
-      decode_record(g, rec.data(), dl.data(), (uint32_t)k, b, c->B, mu, &h_tgt[k], &h_w[k],
+      decode_record(g, rec.data(), (uint32_t)k, b, c->B, mu, &h_tgt[k], &h_w[k],
                     &h_dly[k]);
   }
   return SD_OK;

@@ -23,18 +23,20 @@ constexpr int kFillChunk = 2048;     // draws ranked per build iteration
 // slot its weight goes to in the block's ring window, (delay - d_min) * B +
 // offset in block for a spike of lag 0: below d_max * B <= 20480, since the
 // window fits the LDS.
-//   WF_FP32        u64: low word FP32 weight bits, high word the slot (bits
-//                  0-15) and delay - d_min (bits 16-23, read by plastic nets)
+//   WF_FP32        u32: FP32 weight bits; the u16 slots are an array of their
+//                  own after the weights
 //   WF_BF16        u32: low half BF16 weight, high half the slot
 //   WF_BF16_RESID  u32: low half BF16 residual d (w = mu (1 + d)), high half
 //   and WF_PACKED  the slot
-// All forms but the packed one also keep a u8 delay array (exports).  A record
-// of target and delay took a second load and a multiply-add per synapse: 20
+// Exports take the delay from the slot.  A record of target and delay took a second load and a multiply-add per synapse: 20
 // slices of the 112,500-neuron net in FP32 660 -> 619 us, 14 of 16 sweep nets
-// 5640 -> 5092 us.
+// 5640 -> 5092 us.  The FP32 form's two arrays hold 6 bytes a synapse where one
+// 8-byte record has two unused: 20 slices of 112,500 neurons 607 -> 595 us (the
+// walk runs at the rate of a copy), plastic 1103 -> 1050, a small net's step the
+// same.
 constexpr int kSynSlotBits = 16;
-// kernel forms: records of 8 bytes, or of 4 (the BF16 forms differ in their
-// fixed-point constants only)
+// kernel forms: a weight and a slot, or records of 4 bytes (the BF16 forms
+// differ in their fixed-point constants only)
 enum { KF_F32 = 0, KF_16 = 1 };
 
 // Everything a slice launch needs (passed by value).
@@ -42,7 +44,7 @@ struct SliceArgs {
   // network layout
   const uint2* seg;        // [n_src][NB]: (first synapse, count) of source s in block b
   int64_t n_src;           // source ids
-  const void* syn;         // synapse records (layout per weight form)
+  const void* syn;         // synapse records, or weights and slots (by weight form)
   int64_t N;               // local neurons
   int32_t NB, B;           // blocks, neurons per block
   int32_t K;               // in-degree: block b's synapses start at b * B * K
@@ -93,6 +95,7 @@ struct SliceArgs {
   // list entry (one per spiking neuron and slice, src << 5) the slice's lag
   // mask (bit l: a spike at lag l) and the source's spike before the slice
   int32_t plastic;
+  uint32_t rows_inv;       // ceil(2^32 / B)
   uint64_t* pmask;
   int32_t* pbefore;
   const uint32_t* in_aux;
@@ -142,7 +145,7 @@ struct BuildArgs {
   void* wbits;                   // u8 low weight bytes, or f32 weights
   int32_t tbits, H;
   void* syn;
-  uint8_t* syn_dly;
+  uint16_t* slots;         // window slots (FP32 form)
   int32_t wform;
   int32_t d_min;
   const void* wtab_e;      // encoded weight per quantile index (f32 or bf16 bits)
@@ -210,7 +213,7 @@ hipError_t launch_fill(hipStream_t s, const BuildArgs& a);
 hipError_t launch_seg_pairs(hipStream_t s, const BuildArgs& a);
 hipError_t launch_gather_block(hipStream_t s, const uint2* seg, int64_t n_src, int32_t NB,
                                int32_t b, const int64_t* dst_off, const void* syn,
-                               const uint8_t* dly, int32_t rec_bytes, void* out, uint8_t* out_dly);
+                               const uint16_t* slots, void* out);
 // one fused slice of a batch: workgroup gx serves block map[gx].y of
 // network map[gx].x, arguments in device memory
 hipError_t launch_slice(hipStream_t s, const SliceArgs* d_args, const int2* d_map,

@@ -335,16 +335,14 @@ __global__ void __launch_bounds__(kFillThreads) k_fill(BuildArgs a) {
         float w;
         if (a.fixed) w = inh ? a.w_fix_i : a.w_fix_e;
         else w = inh ? ((const float*)a.wtab_i)[widx] : ((const float*)a.wtab_e)[widx];
-        ((uint64_t*)a.syn)[pos] =
-            ((uint64_t)(slot | ((dly - (uint32_t)a.d_min) << kSynSlotBits)) << 32) |
-            (uint64_t)__float_as_uint(w);
+        ((float*)a.syn)[pos] = w;
+        a.slots[pos] = (uint16_t)slot;
       } else {
         uint32_t wb;
         if (a.fixed) wb = inh ? a.fix_bits_i : a.fix_bits_e;
         else wb = inh ? ((const uint16_t*)a.wtab_i)[widx] : ((const uint16_t*)a.wtab_e)[widx];
         ((uint32_t*)a.syn)[pos] = (wb & 0xffffu) | (slot << kSynSlotBits);
       }
-      if (a.wform != WF_PACKED) a.syn_dly[pos] = (uint8_t)dly;
     }
     __syncthreads();
     for (int p = tid; p < n_in; p += kFillThreads) {
@@ -375,17 +373,17 @@ __global__ void k_seg_pairs(const uint32_t* row, int64_t n_src, int32_t NB, uint
 // Block b's segments gathered source by source (export): dst_off[s] is the
 // first output record of source s.
 __global__ void k_gather_block(const uint2* seg, int64_t n_src, int32_t NB, int32_t b,
-                               const int64_t* dst_off, const void* syn, const uint8_t* dly,
-                               int32_t rec_bytes, void* out, uint8_t* out_dly) {
+                               const int64_t* dst_off, const void* syn, const uint16_t* slots,
+                               void* out) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= n_src) return;
   const uint2 sg = seg[s * NB + b];
   const int64_t o = dst_off[s];
   for (uint32_t k = 0; k < sg.y; ++k) {
     const uint64_t e = (uint64_t)sg.x + k;
-    if (rec_bytes == 8) ((uint64_t*)out)[o + k] = ((const uint64_t*)syn)[e];
+    if (slots)
+      ((uint2*)out)[o + k] = make_uint2(((const uint32_t*)syn)[e], slots[e]);
     else ((uint32_t*)out)[o + k] = ((const uint32_t*)syn)[e];
-    if (dly) out_dly[o + k] = dly[e];
   }
 }
 
@@ -819,7 +817,7 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(BinArgs args) {
 // ---------------------------------------------------------------------------
 // Raw synapse record as loaded (decoded only when its add is issued, so a
 // wave keeps one to three registers per segment in flight).
-// KF: KF_F32 (8-byte records, plastic nets too) or KF_16 (4-byte records).
+// KF: KF_F32 (a weight and a slot, plastic nets too) or KF_16 (4-byte records).
 template <int KF> struct SynRaw;
 template <> struct SynRaw<KF_F32> { uint2 r; };
 template <> struct SynRaw<KF_16> { uint32_t r; };
@@ -840,17 +838,28 @@ constexpr int kMaxGroup = 32;
 constexpr uint32_t kOobIndex = 1u << 28;
 constexpr int kBufWord3 = 0x00020000;  // gfx9 buffer resource: 32-bit dword format
 
+// The block-major table: records, or weights and (FP32 form) slots after them.
+template <int KF> struct SynTable {
+  const uint32_t* w;
+  const uint16_t* slot;
+};
+template <int KF>
+__device__ __forceinline__ SynTable<KF> syn_table(const SliceArgs& a) {
+  SynTable<KF> s = {(const uint32_t*)a.syn, nullptr};
+  if constexpr (KF == KF_F32) s.slot = (const uint16_t*)(s.w + a.N * (int64_t)a.K);
+  return s;
+}
+
 // Record i of the block-major table (index 0 for a lane or slot with
 // nothing to load: the table always holds a record there, the value is
-// not used).  The u8 delay array is for exports: every record holds its
-// window slot, and a walk that also read a delay per synapse touched one to
-// two more lines of every segment (9 and 5 bytes per event instead of 8 and
+// not used).  A walk that read a u8 delay beside target and weight touched one
+// to two more lines of every segment (9 and 5 bytes per event instead of 6 and
 // 4).
 template <int KF>
-__device__ __forceinline__ SynRaw<KF> syn_fetch(const void* syn, uint32_t i) {
+__device__ __forceinline__ SynRaw<KF> syn_fetch(SynTable<KF> s, uint32_t i) {
   SynRaw<KF> x;
-  if constexpr (KF == KF_F32) x.r = ((const uint2*)syn)[i];
-  else x.r = ((const uint32_t*)syn)[i];
+  if constexpr (KF == KF_F32) x.r = make_uint2(s.w[i], s.slot[i]);
+  else x.r = s.w[i];
   return x;
 }
 
@@ -865,7 +874,7 @@ __device__ __forceinline__ void syn_decode(const SynRaw<KF>& x, float m0, float 
   float w;
   if constexpr (KF == KF_F32) {
     w = __uint_as_float(x.r.x);
-    slot = (int)(x.r.y & ((1u << kSynSlotBits) - 1u));
+    slot = (int)x.r.y;
   } else {
     w = __uint_as_float(x.r << 16);
     slot = (int)(x.r >> kSynSlotBits);
@@ -1018,6 +1027,7 @@ __device__ __forceinline__ void walk_chunk(const SliceArgs& a, const uint2* desc
                                            const uint32_t* meta, int n_c, int* s_next,
                                            long long* win, int lane, F in_flight) {
   constexpr int G = SynGroup<KF>::n;
+  const SynTable<KF> tab = syn_table<KF>(a);
   const float m0e = in_vgpr(a.wm0_e), m0i = in_vgpr(a.wm0_i);
   const float m1e = in_vgpr(a.wm1_e), m1i = in_vgpr(a.wm1_i);
   for (;;) {
@@ -1032,7 +1042,7 @@ __device__ __forceinline__ void walk_chunk(const SliceArgs& a, const uint2* desc
     for (int u = 0; u < G; ++u) {
       const uint2 d = desc[g0 + u];  // past the chunk: stale or padding, masked
       const bool on = (u < n_here) & (lane < (int)d.y) & (d.x != 0xffffffffu);
-      raw[u] = syn_fetch<KF>(a.syn, on ? d.x + (uint32_t)lane : 0u);
+      raw[u] = syn_fetch<KF>(tab, on ? d.x + (uint32_t)lane : 0u);
     }
     in_flight();
     uint32_t mt[G];
@@ -1064,7 +1074,7 @@ __device__ __forceinline__ void walk_chunk(const SliceArgs& a, const uint2* desc
         const bool inh = (int)m < 0;
         for (int e0 = 64; e0 < sl; e0 += 64) {
           const bool on = lane + e0 < sl;
-          const SynRaw<KF> x = syn_fetch<KF>(a.syn, on ? d.x + (uint32_t)(e0 + lane) : 0u);
+          const SynRaw<KF> x = syn_fetch<KF>(tab, on ? d.x + (uint32_t)(e0 + lane) : 0u);
           if (on) {
             int slot, v;
             syn_decode<KF>(x, inh ? m0i : m0e, inh ? m1i : m1e, slot, v);
@@ -1090,6 +1100,7 @@ __device__ __forceinline__ void walk_short(const SliceArgs& a, const uint2* desc
                                            long long* win, int lane, F in_flight) {
   constexpr int SPS = 64 / LPS;        // segments per slot
   constexpr int G = LPS == 16 ? 4 : 6; // slots per group
+  const SynTable<KF> tab = syn_table<KF>(a);
   const float m0e = in_vgpr(a.wm0_e), m0i = in_vgpr(a.wm0_i);
   const float m1e = in_vgpr(a.wm1_e), m1i = in_vgpr(a.wm1_i);
   const int sub = lane / LPS, sl = lane & (LPS - 1);
@@ -1117,7 +1128,7 @@ __device__ __forceinline__ void walk_short(const SliceArgs& a, const uint2* desc
       const uint2 d = desc[i];
       mt[u] = meta[i];
       cnt[u] = i < n_c ? (int)d.y : 0;
-      raw[u] = syn_fetch<KF>(a.syn, sl < cnt[u] ? d.x + (uint32_t)sl : 0u);
+      raw[u] = syn_fetch<KF>(tab, sl < cnt[u] ? d.x + (uint32_t)sl : 0u);
       any_long |= cnt[u] > LPS;
     }
     in_flight();
@@ -1132,7 +1143,7 @@ __device__ __forceinline__ void walk_short(const SliceArgs& a, const uint2* desc
         const uint32_t m = meta[i];
         const int n = i < n_c ? (int)d.y : 0;
         for (int e = LPS + sl; __any(e < n); e += LPS)
-          if (e < n) add(syn_fetch<KF>(a.syn, d.x + (uint32_t)e), m);
+          if (e < n) add(syn_fetch<KF>(tab, d.x + (uint32_t)e), m);
       }
     }
   }
@@ -1147,19 +1158,27 @@ __device__ __forceinline__ void walk_any(int lps, const SliceArgs& a, const uint
   else walk_short<KF, 16>(a, desc, meta, n_c, s_next, win, lane, in_flight);
 }
 
+// Row (delay - d_min) of a window slot.  inv = ceil(2^32 / B), B from 2 on:
+// exact, as slot * (inv * B - 2^32) < 2^15 * 2^10 stays below 2^32.
+__device__ __forceinline__ int slot_row(uint32_t slot, uint32_t inv) {
+  return (int)__umulhi(slot, inv);
+}
+
 // The same walk for a plastic net: each lane's synapse takes the entry's
 // spikes in lag order (static inhibitory ones only add), its weight updated
-// before each add and stored back.  Bound by the rule's vector instructions
-// (two exponentials per spike): 20 slices of the 112,500-neuron net took 1160
+// before each add and stored back.  Bound by the table's bytes (6 read and 4
+// written per synapse; weights on their own, so that the stores fill whole
+// sectors: 1103 -> 1050 us against 8-byte records) and the rule's vector
+// instructions (two exponentials per spike): before that, 20 slices of the 112,500-neuron net took 1160
 // us with the rule's constants read from the arguments per synapse and the
 // histories one slot at a time, 1098 with both read per group (1140 with
 // groups of 6).
 __device__ __forceinline__ void plastic_synapse(const SliceArgs& a, const PairRule& rule, uint2 r,
                                                 uint32_t at, bool inh, uint32_t lm, int32_t tprev,
                                                 uint64_t pm, int32_t pb, long long* win,
-                                                int64_t w_lo, int Dmin, int B) {
+                                                int64_t w_lo, int Dmin, int B, uint32_t inv) {
   float w = __uint_as_float(r.x);
-  const int slot = (int)(r.y & ((1u << kSynSlotBits) - 1u));
+  const int slot = (int)r.y;
   if (inh) {
     const int v = (int)(rule.m1i * w);
     while (lm) {
@@ -1170,10 +1189,10 @@ __device__ __forceinline__ void plastic_synapse(const SliceArgs& a, const PairRu
                              __HIP_MEMORY_SCOPE_WORKGROUP);
     }
   } else {
-    const int q = (int)(r.y >> kSynSlotBits), jl = slot - q * B;
+    const int q = slot_row(r.y, inv), jl = slot - q * B;
     w = plastic_walk(rule, w, Dmin + q, pm, pb, lm, tprev, (int32_t)(w_lo - Dmin), (int32_t)w_lo,
                      Dmin, B, jl, win);
-    ((uint32_t*)a.syn)[2 * (size_t)at] = __float_as_uint(w);
+    ((float*)a.syn)[at] = w;
   }
 }
 
@@ -1185,6 +1204,8 @@ __device__ __forceinline__ void walk_plastic(const SliceArgs& a, const uint2* de
                                              long long* win, int64_t w_lo, int Dmin, int B,
                                              int lane, F in_flight) {
   constexpr int G = SynGroup<KF_F32>::n;
+  const SynTable<KF_F32> tab = syn_table<KF_F32>(a);
+  const uint32_t rows_inv = a.rows_inv;
   // read per synapse from the arguments, each constant costs a scalar load and
   // a wait that the LDS adds before it share
   const PairRule rule = {in_vgpr(a.stdp_ap),   in_vgpr(a.stdp_am), in_vgpr(a.stdp_kp),
@@ -1202,7 +1223,7 @@ __device__ __forceinline__ void walk_plastic(const SliceArgs& a, const uint2* de
     for (int u = 0; u < G; ++u) {
       const uint2 d = desc[g0 + u];  // past the chunk: stale or padding, masked
       const bool on = (u < n_here) & (lane < (int)d.y) & (d.x != 0xffffffffu);
-      raw[u] = syn_fetch<KF_F32>(a.syn, on ? d.x + (uint32_t)lane : 0u);
+      raw[u] = syn_fetch<KF_F32>(tab, on ? d.x + (uint32_t)lane : 0u);
     }
     in_flight();
     uint32_t mt[G];
@@ -1218,8 +1239,7 @@ __device__ __forceinline__ void walk_plastic(const SliceArgs& a, const uint2* de
     int32_t hb[G];
 #pragma unroll
     for (int u = 0; u < G; ++u) {
-      const int slot = (int)(raw[u].r.y & ((1u << kSynSlotBits) - 1u));
-      const int q = (int)(raw[u].r.y >> kSynSlotBits), jl = slot - q * B;
+      const int jl = (int)raw[u].r.y - slot_row(raw[u].r.y, rows_inv) * B;
       const int at = (u < n_here && lane < (int)(mt[u] & 127u)) ? jl : 0;
       hm[u] = pm[at];
       hb[u] = pb[at];
@@ -1233,7 +1253,7 @@ __device__ __forceinline__ void walk_plastic(const SliceArgs& a, const uint2* de
       const uint32_t sx = __builtin_amdgcn_readfirstlane(desc[g0 + u].x);
       if ((u < n_here) & (lane < (int)(m & 127u)) & (lane < 64))
         plastic_synapse(a, rule, raw[u].r, sx + (uint32_t)lane, (int32_t)m < 0, lm, tp0, hm[u], hb[u],
-                        win, w_lo, Dmin, B);
+                        win, w_lo, Dmin, B, rows_inv);
     }
     // segments longer than one wave
     if (__builtin_amdgcn_readfirstlane((int)any_long)) {
@@ -1244,10 +1264,10 @@ __device__ __forceinline__ void walk_plastic(const SliceArgs& a, const uint2* de
         for (int e0 = 64; e0 < sl; e0 += 64) {
           if (lane + e0 >= sl) continue;
           const uint32_t at = d.x + (uint32_t)(e0 + lane);
-          const uint2 r = syn_fetch<KF_F32>(a.syn, at).r;
-          const int jl = (int)(r.y & ((1u << kSynSlotBits) - 1u)) - (int)(r.y >> kSynSlotBits) * B;
+          const uint2 r = syn_fetch<KF_F32>(tab, at).r;
+          const int jl = (int)r.y - slot_row(r.y, rows_inv) * B;
           plastic_synapse(a, rule, r, at, (int32_t)m < 0, lagm[g0 + u], tpv[g0 + u], pm[jl], pb[jl], win,
-                          w_lo, Dmin, B);
+                          w_lo, Dmin, B, rows_inv);
         }
       }
     }
@@ -1970,7 +1990,7 @@ __global__ void __launch_bounds__(kSliceThreads) k_slice1(SingleArgs s) {
 // fence.
 // Per slice, one launch per slice against this kernel (stretches of 20 to 100
 // slices): 1,250-neuron delta net 14.9 -> 6.7 us, 30,011 alpha neurons 22.5 ->
-// 11, 112,500 packed 32.8 -> 22, FP32 37.6 -> 25, one-step slices 20.5 -> 8.7.
+// 11, 112,500 packed 32.8 -> 22, FP32 37.6 -> 24, one-step slices 20.5 -> 8.7.
 // Three polls in flight instead of one were 2% slower, spike groups split
 // evenly over the waves 1-3%.
 constexpr int64_t kBarSpin = 1LL << 22;  // polls before a wait gives up (explicit mode)
@@ -2748,9 +2768,9 @@ hipError_t launch_fill(hipStream_t s, const BuildArgs& a) {
 
 hipError_t launch_gather_block(hipStream_t s, const uint2* seg, int64_t n_src, int32_t NB,
                                int32_t b, const int64_t* dst_off, const void* syn,
-                               const uint8_t* dly, int32_t rec_bytes, void* out, uint8_t* out_dly) {
+                               const uint16_t* slots, void* out) {
   hipLaunchKernelGGL(k_gather_block, dim3((unsigned)((n_src + 255) / 256)), dim3(256), 0, s, seg,
-                     n_src, NB, b, dst_off, syn, dly, rec_bytes, out, out_dly);
+                     n_src, NB, b, dst_off, syn, slots, out);
   return hipGetLastError();
 }
 
