@@ -303,7 +303,10 @@ struct sd_ctx {
   int persist_fit = -1;     // the plan fits and all blocks are resident (-1: not yet asked)
   PersistPlan plan{};
   void* xch = nullptr;      // exchange lines of a persistent launch
-  uint32_t epoch = 0;       // slices published so far (line tags, modulo 2^16)
+  // line tags given out so far (modulo 2^16).  Every one is published: two
+  // tags later a line is always rewritten, so no line still holds the tag of
+  // 65,536 before
+  uint32_t epoch = 0;
   int64_t bar_spin = -1;    // polls before a wait gives up (< 0: default)
 };
 
@@ -1568,7 +1571,7 @@ sd_status run_persistent(sd_ctx* c, int32_t S, bool* done) {
   }
   HIP_TRY(c, e);
   *done = true;
-  c->epoch += (uint32_t)S;
+  c->epoch += (uint32_t)(S - 1);  // the last slice's spikes go to the list, not to a line
   c->cur ^= S & 1;
   c->ci = (c->ci + 1) % 3;
   c->pend_open = true;

@@ -229,6 +229,25 @@ struct PersistPlan {
   int32_t cap;      // spikes per walk chunk
   size_t lds;
 };
+// Arguments of a persistent launch (passed by value).
+struct PersistArgs {
+  SliceArgs a;         // network constants
+  uint32_t* lists[2];  // the two spike-list buffers
+  int32_t* cnt3;       // the three rotating list counters
+  int32_t cur0, ci0;   // slice 0 reads lists[cur0] with count cnt3[ci0]
+  int32_t pend0;       // slice 0 delivers that list (else no delivery)
+  int32_t S;           // slices
+  int32_t per_xcd;     // blocks per XCD (grid = 8 * per_xcd)
+  int32_t cap;         // spikes per walk chunk
+  int32_t drows;       // drive-count rows (d_min, or whole 8-step chunks)
+  int32_t crows;       // carry rows in LDS
+  int32_t helpers;     // waves without a neuron draw the drive during the update
+  uint32_t epoch0;     // tag of slice 0's line (slices 0..S-2 write theirs)
+  int64_t t0;          // first step of slice 0
+  int64_t rb_hi0;      // HBM ring rows of steps below this hold earlier sums
+  uint64_t* xch;       // exchange lines [2][NB][kXchWords]
+  int64_t spin_limit;  // polls before a wait gives up
+};
 constexpr int kPersistMaxNB = 512;  // two 1024-thread workgroups per compute unit
 bool persist_plan(int32_t B, int32_t Dmin, int32_t Dmax, size_t budget, PersistPlan* plan);
 size_t xch_bytes(int32_t NB);  // exchange lines of NB blocks
