@@ -2464,6 +2464,10 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
         for (int i = kXchMax + tid; i < n_lds; i += kSliceThreads)
           __hip_atomic_store(olist + (size_t)b * B * Dmin + i, list_entry(i), __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
+        // every storing wave waits for its own entries (those past the LDS list
+        // too) to be out before the barrier, which waits for no stores; wave 0,
+        // which writes the line, orders them before it
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __syncthreads();
         if (wv == 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       }
