@@ -253,7 +253,10 @@ sd_status sd_set_count_mode(sd_ctx* ctx, int32_t on);
  * all blocks fit on the device at once; SD_ESTATE before
  * sd_build_connections.  A wait for other blocks' spikes past its spin limit
  * sets bit 4 of sd_stats.overflow and ends the launch early (the run's
- * results are then invalid). */
+ * results are then invalid).  Where that launch was not asked for by this
+ * call, every call that reads the net back (state, ring, spikes, pending,
+ * checkpoint) and then every call that would advance it returns SD_EOVERFLOW
+ * too, until sd_load_state. */
 sd_status sd_set_persistent(sd_ctx* ctx, int32_t max_slices);
 
 /* For callers that watch a persistent run (and for tests of its failure

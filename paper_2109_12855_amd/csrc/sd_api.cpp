@@ -308,6 +308,13 @@ struct sd_ctx {
   // 65,536 before
   uint32_t epoch = 0;
   int64_t bar_spin = -1;    // polls before a wait gives up (< 0: default)
+  // A launch that nobody asked for and that ended early has advanced the net
+  // part of the way only: its serial stays in *ended (device), the calls that
+  // wait for the stream look there (watch: such a launch since the last look)
+  // and report it, and a lost net runs no further until a checkpoint is loaded.
+  uint32_t* ended = nullptr;
+  uint32_t persist_n = 0;   // persistent launches so far (their serials)
+  bool watch = false, lost = false;
 };
 
 // Independent networks advanced together: every slice of all members is
@@ -518,6 +525,27 @@ hipError_t read_back(sd_ctx* c, const Piece* p, int n) {
   return e;
 }
 
+// SD_OK unless a persistent launch that nobody asked for ended early.
+sd_status not_lost(sd_ctx* c) {
+  return c->lost ? fail(c, SD_EOVERFLOW, "a persistent launch ended early (a wait for other "
+                        "blocks' spikes passed its limit); what followed is invalid until a "
+                        "checkpoint is loaded")
+                 : SD_OK;
+}
+// The same once the stream has been waited for, with the word read then (where
+// there is one to read).
+sd_status not_lost(sd_ctx* c, uint32_t ended) {
+  if (c->watch && (ended & kPersistUnasked)) c->lost = true;
+  c->watch = false;
+  return not_lost(c);
+}
+sd_status sync_not_lost(sd_ctx* c) {
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  uint32_t ended = 0;
+  if (c->watch) HIP_TRY(c, hipMemcpy(&ended, c->ended, 4, hipMemcpyDeviceToHost));
+  return not_lost(c, ended);
+}
+
 bool open_loop(const sd_config& c) { return c.n_src_exc > 0; }
 
 int32_t auto_block(const sd_config& c, int64_t N) {
@@ -567,6 +595,8 @@ sd_status check_config(const sd_config* c, std::string* why) {
 }
 
 // Everything sizes-related in one place, shared by query and create.
+constexpr size_t kCntWord = 4;  // first list counter of its block (word 0: early end)
+
 struct Layout {
   sd_sizes sz;
   int64_t N, n_src, n_syn, M, n_tiles, rec_cap;
@@ -769,10 +799,12 @@ sd_status make_layout(const sd_config* c, Layout* L, std::string* why) {
   L->off_y1 = take((size_t)L->N * 4);
   L->off_y2 = take((size_t)L->N * 4);
   L->off_r = take((size_t)L->N * 4);
+  // the word a persistent launch that ended early leaves, within one transfer
+  // of the neurons' state, and the three list counters
+  L->off_cnt = take((kCntWord + 3) * 4);
   L->off_rb = take((size_t)c->ring_len * L->N * 4);
   L->off_list0 = take((size_t)L->list_cap * 4);
   L->off_list1 = take((size_t)L->list_cap * 4);
-  L->off_cnt = take(3 * 4);
   L->off_rec = take((size_t)std::max<int64_t>(L->rec_cap, 1) * 8);
   L->off_wte = take(65536 * 4);
   L->off_wti = take(65536 * 4);
@@ -1118,7 +1150,8 @@ sd_status sd_create(const sd_config* cfg, void* hip_stream, void* d_arena, size_
     c->prev[0] = (int32_t*)(A + L.off_prev0);
     c->prev[1] = (int32_t*)(A + L.off_prev1);
   }
-  c->cnt3 = (int32_t*)(A + L.off_cnt);
+  c->ended = (uint32_t*)(A + L.off_cnt);
+  c->cnt3 = (int32_t*)(A + L.off_cnt) + kCntWord;
   c->rec = (uint2*)(A + L.off_rec);
   c->wtab_e = A + L.off_wte;
   c->wtab_i = A + L.off_wti;
@@ -1182,7 +1215,7 @@ sd_status sd_create(const sd_config* cfg, void* hip_stream, void* d_arena, size_
                             c->stream));
   HIP_TRY(c, hipMemsetAsync(c->counters, 0, 8 * 8, c->stream));
   HIP_TRY(c, hipMemsetAsync(c->overflow, 0, 4, c->stream));
-  HIP_TRY(c, hipMemsetAsync(c->cnt3, 0, 3 * 4, c->stream));
+  HIP_TRY(c, hipMemsetAsync(c->ended, 0, (kCntWord + 3) * 4, c->stream));
   if (g.plastic) {  // no spikes yet: empty histories, no earlier spike (-1)
     HIP_TRY(c, hipMemsetAsync(c->pmask, 0, (size_t)c->N * 8, c->stream));
     HIP_TRY(c, hipMemsetAsync(c->pbefore, 0xff, (size_t)c->N * 4, c->stream));
@@ -1327,6 +1360,7 @@ sd_status sd_get_sizes(const sd_ctx* c, sd_sizes* out) {
 sd_status sd_update_neurons(sd_ctx* c, int32_t n_steps) {
   if (!c || n_steps < 1) return fail(c, SD_EINVAL, "n_steps must be >= 1");
   if (!c->built) return fail(c, SD_ESTATE, "build_connections first");
+  if (not_lost(c) != SD_OK) return SD_EOVERFLOW;
   const int32_t Dmin = c->cfg.d_min;
   const int64_t in_slice = c->t_now % Dmin;
   if (in_slice + n_steps > Dmin)
@@ -1398,6 +1432,7 @@ namespace {
 sd_status deliver_impl(sd_ctx* c, bool own, const uint32_t* d_src, const uint8_t* d_lag,
                        int64_t n, int64_t t0, uint32_t* list, int32_t* list_cnt, int64_t cap) {
   if (!c->built) return fail(c, SD_ESTATE, "build_connections first");
+  if (not_lost(c) != SD_OK) return SD_EOVERFLOW;
   const sd_config& g = c->cfg;
   SliceArgs a = base_args(c);
   a.do_deliver = 1;
@@ -1457,6 +1492,7 @@ namespace {
 // pending slice (if any), update m <= d_min steps, and start a new list;
 // advances the host state as if the launch had run.
 sd_status next_fused_slice(sd_ctx* c, int32_t m, SliceArgs* out) {
+  if (not_lost(c) != SD_OK) return SD_EOVERFLOW;
   const sd_config& g = c->cfg;
   const int32_t Dmin = g.d_min;
   SliceArgs a = base_args(c);
@@ -1521,6 +1557,7 @@ bool persist_kind(const sd_ctx* c) {
 // steps to go (0: one launch per slice).
 sd_status persist_slices(sd_ctx* c, int64_t left, int32_t* S) {
   *S = 0;
+  if (not_lost(c) != SD_OK) return SD_EOVERFLOW;
   const int32_t Dmin = c->cfg.d_min;
   if (c->persist == 0 || left < Dmin) return SD_OK;
   if (c->pend_open && c->pend_t0 + Dmin != c->t_now) return SD_OK;
@@ -1558,19 +1595,24 @@ sd_status run_persistent(sd_ctx* c, int32_t S, bool* done) {
   const sd_config& g = c->cfg;
   const int32_t Dmin = g.d_min;
   const SliceArgs a = base_args(c);
+  const bool unasked = c->persist == kPersistAuto;
   const int64_t spin = c->bar_spin >= 0 ? c->bar_spin
-                       : c->persist == kPersistAuto ? kPersistAutoSpin : -1;
+                       : unasked ? kPersistAutoSpin : -1;
   *done = false;
+  c->persist_n = c->persist_n % (kPersistUnasked - 1) + 1;
+  const uint32_t serial = c->persist_n | (unasked ? kPersistUnasked : 0u);
   const hipError_t e =
       launch_persist(c->stream, a, c->list, c->cnt3, c->cur, c->ci, c->pend_open ? 1 : 0, S,
-                     c->t_now, c->rb_hi, c->xch, c->epoch + 1, spin, c->plan, g.wform);
-  if (e != hipSuccess && c->persist == kPersistAuto) {
+                     c->t_now, c->rb_hi, c->xch, c->epoch + 1, spin, c->ended, serial, c->plan,
+                     g.wform);
+  if (e != hipSuccess && unasked) {
     (void)hipGetLastError();
     c->persist_fit = 0;
     return SD_OK;
   }
   HIP_TRY(c, e);
   *done = true;
+  c->watch |= unasked;
   c->epoch += (uint32_t)(S - 1);  // the last slice's spikes go to the list, not to a line
   c->cur ^= S & 1;
   c->ci = (c->ci + 1) % 3;
@@ -1724,7 +1766,8 @@ sd_status sd_get_stats(sd_ctx* c, sd_stats* out) {
   if (!c || !out) return SD_EINVAL;
   unsigned long long cnt[4];
   int32_t ov = 0;
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  const sd_status s = sync_not_lost(c);
+  if (s != SD_OK && s != SD_EOVERFLOW) return s;
   HIP_TRY(c, hipMemcpy(cnt, c->counters, sizeof cnt, hipMemcpyDeviceToHost));
   HIP_TRY(c, hipMemcpy(&ov, c->overflow, 4, hipMemcpyDeviceToHost));
   out->t_now = c->t_now;
@@ -1735,7 +1778,7 @@ sd_status sd_get_stats(sd_ctx* c, sd_stats* out) {
   out->slices = c->slices;
   out->overflow = ov;
   if (ov & 12) return fail(c, SD_EINVAL, "an external spike list held invalid entries (flags %d)", ov);
-  return ov ? SD_EOVERFLOW : SD_OK;
+  return ov ? SD_EOVERFLOW : s;
 }
 
 sd_status sd_read_ring(sd_ctx* c, float* h_out, int32_t n_slots) {
@@ -1748,23 +1791,27 @@ sd_status sd_read_ring(sd_ctx* c, float* h_out, int32_t n_slots) {
     if (t < c->rb_hi) p.push_back({dst, c->rb + (t % L) * c->N, (size_t)c->N * 4});
     else std::memset(dst, 0, (size_t)c->N * 4);
   }
+  uint32_t ended = 0;
+  if (c->watch) p.push_back({&ended, c->ended, 4});
   if (p.empty()) HIP_TRY(c, hipStreamSynchronize(c->stream));
   HIP_TRY(c, read_back(c, p.data(), (int)p.size()));
-  return SD_OK;
+  return not_lost(c, ended);
 }
 
 sd_status sd_read_state(sd_ctx* c, float* h_v, float* h_y1, float* h_y2, int32_t* h_r) {
   if (!c) return SD_EINVAL;
   const size_t n = (size_t)c->N * 4;
-  Piece p[4];
+  Piece p[5];
   int k = 0;
   if (h_v) p[k++] = {h_v, c->V, n};
   if (h_y1) p[k++] = {h_y1, c->y1, n};
   if (h_y2) p[k++] = {h_y2, c->y2, n};
   if (h_r) p[k++] = {h_r, c->r, n};
+  uint32_t ended = 0;
+  if (c->watch) p[k++] = {&ended, c->ended, 4};
   if (k == 0) HIP_TRY(c, hipStreamSynchronize(c->stream));
   HIP_TRY(c, read_back(c, p, k));
-  return SD_OK;
+  return not_lost(c, ended);
 }
 
 sd_status sd_write_state(sd_ctx* c, const float* h_v, const float* h_y1, const float* h_y2,
@@ -1819,7 +1866,7 @@ sd_status sd_save_state(sd_ctx* c, void* h_buf, size_t cap, size_t* used) {
   if (!c || !used) return SD_EINVAL;
   if (c->cfg.plastic)
     return fail(c, SD_EUNSUPPORTED, "checkpoints of plastic nets (their weights are state)");
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  if (sd_status s = sync_not_lost(c)) return s;
   const int32_t L = c->cfg.ring_len;
   int64_t n_pend = 0;
   if (c->pend_open && !open_loop(c->cfg)) {
@@ -1909,6 +1956,9 @@ sd_status sd_load_state(sd_ctx* c, const void* h_buf, size_t n) {
   c->slices = hd.slices;
   c->count_mode = hd.count_mode;
   c->rec_read = 0;
+  const uint32_t none = 0;
+  HIP_TRY(c, hipMemcpy(c->ended, &none, 4, hipMemcpyHostToDevice));
+  c->watch = c->lost = false;
   return SD_OK;
 }
 
@@ -1916,7 +1966,7 @@ sd_status sd_get_spikes(sd_ctx* c, int64_t* h_step, uint32_t* h_id, int64_t cap,
   if (!c || !n) return SD_EINVAL;
   *n = 0;
   if (c->rec_cap == 0) return fail(c, SD_ESTATE, "spike recording is off");
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  if (sd_status s = sync_not_lost(c)) return s;
   unsigned long long total = 0;
   HIP_TRY(c, hipMemcpy(&total, c->counters + 3, 8, hipMemcpyDeviceToHost));
   const int64_t avail = std::min<int64_t>((int64_t)total, c->rec_cap) - c->rec_read;
@@ -1940,7 +1990,7 @@ sd_status sd_get_pending(sd_ctx* c, uint32_t* h_src, uint8_t* h_lag, int64_t cap
   *n = 0;
   if (slice_t0) *slice_t0 = c->pend_open ? c->pend_t0 : -1;
   if (!c->pend_open || open_loop(c->cfg)) return SD_OK;
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  if (sd_status s = sync_not_lost(c)) return s;
   int32_t cnt = 0;
   HIP_TRY(c, hipMemcpy(&cnt, c->cnt3 + c->ci, 4, hipMemcpyDeviceToHost));
   const int64_t nl = std::min<int64_t>(cnt, c->list_cap);
@@ -2362,6 +2412,8 @@ sd_status sd_batch_simulate_steps(sd_batch* bt, int64_t n_steps) {
     if (!bt->nets[i]->built) return bfail(bt, SD_ESTATE, "build the batch first");
     if (bt->nets[i]->t_now != t0)
       return bfail(bt, SD_ESTATE, "members were advanced separately (t_now differs)");
+    if (not_lost(bt->nets[i]) != SD_OK)
+      return bfail(bt, SD_EOVERFLOW, sd_last_error(bt->nets[i]));
   }
   const int32_t Dmin = bt->nets[0]->cfg.d_min;
   std::vector<SliceArgs> queue;  // n argument structs per fused launch

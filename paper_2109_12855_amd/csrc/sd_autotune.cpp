@@ -182,6 +182,8 @@ double time_candidate(const std::vector<sd_config>& cfgs, int32_t warmup, int32_
     ok = ok && hipEventRecord(e0, s) == hipSuccess;
     ok = ok && sd_simulate_steps(c, (int64_t)slices * d_min) == SD_OK;
     ok = ok && hipEventRecord(e1, s) == hipSuccess && hipEventSynchronize(e1) == hipSuccess;
+    // a run that ended early has no time
+    ok = ok && sd_read_state(c, nullptr, nullptr, nullptr, nullptr) == SD_OK;
     float ms = 0.f;
     if (ok && hipEventElapsedTime(&ms, e0, e1) == hipSuccess) us = ms * 1e3 / slices;
     sd_destroy(c);

@@ -247,7 +247,10 @@ struct PersistArgs {
   int64_t rb_hi0;      // HBM ring rows of steps below this hold earlier sums
   uint64_t* xch;       // exchange lines [2][NB][kXchWords]
   int64_t spin_limit;  // polls before a wait gives up
+  uint32_t* ended;     // a wait that gives up stores serial here
+  uint32_t serial;     // this launch; kPersistUnasked: nobody asked for it
 };
+constexpr uint32_t kPersistUnasked = 0x80000000u;
 constexpr int kPersistMaxNB = 512;  // two 1024-thread workgroups per compute unit
 bool persist_plan(int32_t B, int32_t Dmin, int32_t Dmax, size_t budget, PersistPlan* plan);
 size_t xch_bytes(int32_t NB);  // exchange lines of NB blocks
@@ -255,7 +258,8 @@ int persist_occupancy(int wform, const PersistPlan& plan);
 hipError_t launch_persist(hipStream_t s, const SliceArgs& a, uint32_t* const lists[2],
                           int32_t* cnt3, int32_t cur0, int32_t ci0, int32_t pend0, int32_t S,
                           int64_t t0, int64_t rb_hi0, void* xch, uint32_t epoch0,
-                          int64_t spin_limit, const PersistPlan& plan, int wform);
+                          int64_t spin_limit, uint32_t* ended, uint32_t serial,
+                          const PersistPlan& plan, int wform);
 size_t slice_lds_bytes(int B, int Dmin, int win_rows, bool plastic = false, bool bin = false);
 // add shift to the time fields (t_upd, t_slice0, w_lo, rb_hi) of args[0..n)
 hipError_t launch_shift_args(hipStream_t s, SliceArgs* args, int32_t n, int64_t shift);

@@ -2185,13 +2185,17 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
       if (on[i]) put(at + i, sg[i], (uint32_t)blk * (uint32_t)B + (e & 1023u), (int)(e >> 10));
     }
   };
-  // a wait past the limit, or another workgroup's, ends the launch
+  // a wait past the limit, or another workgroup's, ends the launch; so does the
+  // end of an earlier one where nobody asked for either (its state is lost)
   auto give_up = [&](int64_t spins) {
-    if (spins <= pp->spin_limit &&
-        ((spins & 255) != 0 ||
-         !(__hip_atomic_load(a.overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 16)))
-      return false;
+    if (spins <= pp->spin_limit) {
+      if ((spins & 255) != 0) return false;
+      const uint32_t e =
+          __hip_atomic_load(pp->ended, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (e != pp->serial && !(e & pp->serial & kPersistUnasked)) return false;
+    }
     if (lane == 0) {
+      __hip_atomic_store(pp->ended, pp->serial, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       atomicOr(a.overflow, 16);
       s_abort = 1;
     }
@@ -2823,7 +2827,8 @@ int persist_occupancy(int wform, const PersistPlan& plan) {
 hipError_t launch_persist(hipStream_t s, const SliceArgs& a, uint32_t* const lists[2],
                           int32_t* cnt3, int32_t cur0, int32_t ci0, int32_t pend0, int32_t S,
                           int64_t t0, int64_t rb_hi0, void* xch, uint32_t epoch0,
-                          int64_t spin_limit, const PersistPlan& plan, int wform) {
+                          int64_t spin_limit, uint32_t* ended, uint32_t serial,
+                          const PersistPlan& plan, int wform) {
   PersistArgs p;
   p.a = a;
   p.lists[0] = lists[0];
@@ -2843,6 +2848,8 @@ hipError_t launch_persist(hipStream_t s, const SliceArgs& a, uint32_t* const lis
   p.rb_hi0 = rb_hi0;
   p.xch = (uint64_t*)xch;
   p.spin_limit = spin_limit < 0 ? kBarSpin : spin_limit;
+  p.ended = ended;
+  p.serial = serial;
   void* args[] = {&p};
   const dim3 grid((unsigned)(8 * p.per_xcd)), block(kSliceThreads);
   return hipLaunchCooperativeKernel(persist_kernel(wform, plan.carry_lds), grid, block, args,

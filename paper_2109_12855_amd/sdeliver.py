@@ -311,7 +311,8 @@ class Net:
     def set_persistent(self, max_slices: int):
         """Run up to max_slices whole slices per persistent launch (0: one
         launch per slice; a new net runs stretches of 4 and more slices
-        persistently where it can)."""
+        persistently where it can; should such a launch end early, reading the
+        net raises until a checkpoint is loaded)."""
         self._check(lib().sd_set_persistent(self._h, int(max_slices)), "sd_set_persistent")
 
     def set_barrier_spin(self, polls: int):

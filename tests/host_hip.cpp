@@ -24,7 +24,7 @@ std::map<const void*, std::string> names;
 std::vector<Launch> launches;
 Stream null_stream{0, false};
 int device = 0;
-bool no_pinned = false;
+bool no_pinned = false, end_early = false;
 int64_t n_pinned = 0, n_recorded = 0;
 struct { dim3 grid, block; size_t lds; hipStream_t s; } config;
 
@@ -41,6 +41,10 @@ void note(const void* fn, void** args, hipStream_t s) {
     l.f[2] = p->S;
     l.f[3] = p->epoch0;
     l.f[4] = p->a.seg_lanes;
+    if (end_early) {
+      *p->ended = p->serial;
+      *p->a.overflow |= 16;
+    }
   } else if (is(n, "k_slice1")) {
     const auto* a = (const sd::SliceArgs*)args[0];
     l.f[0] = 2;
@@ -63,6 +67,7 @@ int64_t host_launches() { return (int64_t)launches.size(); }
 void host_launch(int64_t i, int64_t* out) { std::memcpy(out, launches[(size_t)i].f, sizeof(Launch)); }
 void host_clear() { launches.clear(); }
 void host_no_pinned(int on) { no_pinned = on; }
+void host_end_early(int on) { end_early = on; }  // persistent launches to come
 int64_t host_pinned() { return n_pinned; }
 int64_t host_recorded() { return n_recorded; }
 void host_capture(void* s, int on) { of((hipStream_t)s)->capturing = on; }
