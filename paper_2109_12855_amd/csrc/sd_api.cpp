@@ -397,53 +397,34 @@ sd_status fail(sd_ctx* c, sd_status s, const char* fmt, ...) {
       return fail(ctx, SD_EHIP, "%s failed: %s", #call, hipGetErrorString(e_));    \
   } while (0)
 
-// Pinned staging of the read-back calls: two halves and an event for each.
-// A call borrows one from its device's free ones (or allocates it, ~0.2 ms)
-// and gives it back; at most kStageKeep stay free, and the last context to go
-// frees them.
+// Pinned staging of the read-back calls, two halves.  A call borrows one from
+// the free ones (or allocates it, ~0.2 ms) and gives it back; at most
+// kStageKeep stay free, and the last context to go frees them.  The memory
+// serves every device: which one is current at a call does not matter.
 constexpr size_t kStageHalf = 1 << 20;
 constexpr size_t kStageKeep = 4;
-struct Stage {
-  int device = -1;
-  char* mem = nullptr;
-  hipEvent_t ev[2] = {nullptr, nullptr};
-};
 struct StagePool {
   std::mutex m;
   int64_t users = 0;  // contexts alive
-  std::vector<Stage> free;
+  std::vector<char*> free;
 };
 StagePool& stage_pool() {
   static StagePool* pool = new StagePool;  // outlives every context
   return *pool;
 }
-void stage_free(Stage& s) {
-  for (int h = 0; h < 2; ++h)
-    if (s.ev[h]) (void)hipEventDestroy(s.ev[h]);
-  if (s.mem) (void)hipHostFree(s.mem);
-  s = Stage();
-}
-hipError_t stage_take(int device, Stage* out) {
+hipError_t stage_take(char** out) {
   StagePool& p = stage_pool();
   {
     std::lock_guard<std::mutex> lock(p.m);
-    for (size_t i = 0; i < p.free.size(); ++i)
-      if (p.free[i].device == device) {
-        *out = p.free[i];
-        p.free.erase(p.free.begin() + (std::ptrdiff_t)i);
-        return hipSuccess;
-      }
+    if (!p.free.empty()) {
+      *out = p.free.back();
+      p.free.pop_back();
+      return hipSuccess;
+    }
   }
-  Stage s;
-  s.device = device;
-  hipError_t e = hipHostMalloc((void**)&s.mem, 2 * kStageHalf, hipHostMallocDefault);
-  for (int h = 0; h < 2 && e == hipSuccess; ++h)
-    e = hipEventCreateWithFlags(&s.ev[h], hipEventDisableTiming);
-  if (e != hipSuccess) stage_free(s);
-  *out = s;
-  return e;
+  return hipHostMalloc((void**)out, 2 * kStageHalf, hipHostMallocPortable);
 }
-void stage_give(Stage& s) {
+void stage_give(char* s) {
   StagePool& p = stage_pool();
   {
     std::lock_guard<std::mutex> lock(p.m);
@@ -452,17 +433,17 @@ void stage_give(Stage& s) {
       return;
     }
   }
-  stage_free(s);
+  (void)hipHostFree(s);
 }
 void stage_user(int64_t d) {
   StagePool& p = stage_pool();
-  std::vector<Stage> gone;
+  std::vector<char*> gone;
   {
     std::lock_guard<std::mutex> lock(p.m);
     p.users += d;
     if (p.users == 0) gone.swap(p.free);
   }
-  for (Stage& s : gone) stage_free(s);
+  for (char* s : gone) (void)hipHostFree(s);
 }
 
 // Device ranges read back into host memory.  A copy into pageable memory
@@ -470,8 +451,9 @@ void stage_user(int64_t d) {
 // here adjacent ranges go as one transfer into pinned memory and from there
 // to their places, long ones through two halves, one half's transfer
 // overlapping the host copy out of the other.  Neuron state (four arrays) of
-// 1,250 / 30,011 / 112,500 / 281,250 neurons: 73 / 69 / 131 / 362 us with a
-// blocking copy per array, 17 / 38 / 94 / 187 us here.
+// 1,250 / 30,011 / 112,500 / 281,250 neurons: 61 / 65 / 129 / 339 us with a
+// blocking copy per array, 15 / 34 / 87 / 157 us here (the last 178 with an
+// event per half to wait for).
 struct Piece {
   void* dst;
   const void* src;
@@ -480,8 +462,8 @@ struct Piece {
 constexpr size_t kStageGap = 256;  // arena padding copied along between ranges
 
 hipError_t read_back(sd_ctx* c, const Piece* p, int n) {
-  Stage st;
-  hipError_t e = stage_take(c->device, &st);
+  char* st = nullptr;
+  hipError_t e = stage_take(&st);
   int i0 = 0;
   while (i0 < n && e == hipSuccess) {
     // pieces [i0, i1) lie one after the other on the device
@@ -494,34 +476,31 @@ hipError_t read_back(sd_ctx* c, const Piece* p, int n) {
       end = q + p[i1].n;
     }
     const size_t total = (size_t)(end - base);
-    // one transfer and one wait where both halves hold it: an event costs as
-    // much as a transfer of some 100 KB
+    // one transfer and one wait where both halves hold it
     const size_t step = total <= 2 * kStageHalf ? std::max<size_t>(total, 1) : kStageHalf;
     const size_t n_ch = (total + step - 1) / step;
     auto issue = [&](size_t k) {
-      const size_t at = k * step, m = std::min(step, total - at);
-      hipError_t x = hipMemcpyAsync(st.mem + (k & 1) * kStageHalf, base + at, m,
-                                    hipMemcpyDeviceToHost, c->stream);
-      if (x == hipSuccess && n_ch > 1) x = hipEventRecord(st.ev[k & 1], c->stream);
-      return x;
+      const size_t at = k * step;
+      return hipMemcpyAsync(st + (k & 1) * kStageHalf, base + at, std::min(step, total - at),
+                            hipMemcpyDeviceToHost, c->stream);
     };
-    for (size_t k = 0; k < n_ch && k < 2 && e == hipSuccess; ++k) e = issue(k);
+    if (n_ch > 0) e = issue(0);
     for (size_t k = 0; k < n_ch && e == hipSuccess; ++k) {
-      e = n_ch > 1 ? hipEventSynchronize(st.ev[k & 1]) : hipStreamSynchronize(c->stream);
+      e = hipStreamSynchronize(c->stream);  // chunk k is in its half
+      if (e == hipSuccess && k + 1 < n_ch) e = issue(k + 1);  // the other half is copied out
       if (e != hipSuccess) break;
-      const char* half = st.mem + (k & 1) * kStageHalf;
+      const char* half = st + (k & 1) * kStageHalf;
       const size_t lo = k * step, hi = std::min(lo + step, total);
       for (int i = i0; i < i1; ++i) {
         const size_t a = (size_t)((const char*)p[i].src - base), b = a + p[i].n;
         const size_t x = std::max(a, lo), y = std::min(b, hi);
         if (x < y) std::memcpy((char*)p[i].dst + (x - a), half + (x - lo), y - x);
       }
-      if (k + 2 < n_ch) e = issue(k + 2);
     }
     i0 = i1;
   }
   if (e != hipSuccess) (void)hipStreamSynchronize(c->stream);  // nothing in flight into the halves
-  if (st.mem) stage_give(st);
+  if (st) stage_give(st);
   return e;
 }
 
