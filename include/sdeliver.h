@@ -107,7 +107,7 @@ typedef struct {
   int32_t k_exc, k_inh;      /* fixed in-degree, drawn with replacement         */
   int32_t d_lo, d_hi;        /* delays uniform over [d_lo, d_hi] steps          */
   int32_t d_min, d_max;      /* network min/max delay; a slice is d_min steps   */
-  int32_t ring_len;          /* ring buffer length L >= d_min + d_max, <= 64    */
+  int32_t ring_len;          /* ring buffer length L >= d_min + d_max, <= 512   */
   double h;                  /* resolution (ms)                                 */
   double w_exc, w_cv, g;     /* E weight mean and CV; I weight = -g * E draw    */
   double tau_m, c_m, tau_syn, e_l, v_th, v_reset, t_ref, i_e;

@@ -402,34 +402,35 @@ sd_status fail(sd_ctx* c, sd_status s, const char* fmt, ...) {
 // kStageKeep stay free, and the last context to go frees them.  The memory
 // serves every device: which one is current at a call does not matter.
 constexpr size_t kStageHalf = 1 << 20;
-constexpr size_t kStageKeep = 4;
+constexpr int kStageKeep = 4;
 struct StagePool {
   std::mutex m;
   int64_t users = 0;  // contexts alive
-  std::vector<char*> free;
+  char* free[kStageKeep] = {};
+  int n_free = 0;
 };
 StagePool& stage_pool() {
-  static StagePool* pool = new StagePool;  // outlives every context
-  return *pool;
+  static StagePool pool;  // no destructor to speak of: outlives every context
+  return pool;
 }
-hipError_t stage_take(char** out) {
+// nullptr where no pinned memory is to be had.
+char* stage_take() {
   StagePool& p = stage_pool();
   {
     std::lock_guard<std::mutex> lock(p.m);
-    if (!p.free.empty()) {
-      *out = p.free.back();
-      p.free.pop_back();
-      return hipSuccess;
-    }
+    if (p.n_free > 0) return p.free[--p.n_free];
   }
-  return hipHostMalloc((void**)out, 2 * kStageHalf, hipHostMallocPortable);
+  char* s = nullptr;
+  if (hipHostMalloc((void**)&s, 2 * kStageHalf, hipHostMallocPortable) == hipSuccess) return s;
+  (void)hipGetLastError();
+  return nullptr;
 }
 void stage_give(char* s) {
   StagePool& p = stage_pool();
   {
     std::lock_guard<std::mutex> lock(p.m);
-    if (p.users > 0 && p.free.size() < kStageKeep) {
-      p.free.push_back(s);
+    if (p.users > 0 && p.n_free < kStageKeep) {
+      p.free[p.n_free++] = s;
       return;
     }
   }
@@ -437,13 +438,15 @@ void stage_give(char* s) {
 }
 void stage_user(int64_t d) {
   StagePool& p = stage_pool();
-  std::vector<char*> gone;
+  char* gone[kStageKeep];
+  int n = 0;
   {
     std::lock_guard<std::mutex> lock(p.m);
     p.users += d;
-    if (p.users == 0) gone.swap(p.free);
+    if (p.users == 0)
+      for (; p.n_free > 0; ++n) gone[n] = p.free[--p.n_free];
   }
-  for (char* s : gone) (void)hipHostFree(s);
+  for (int i = 0; i < n; ++i) (void)hipHostFree(gone[i]);
 }
 
 // Device ranges read back into host memory.  A copy into pageable memory
@@ -461,9 +464,18 @@ struct Piece {
 };
 constexpr size_t kStageGap = 256;  // arena padding copied along between ranges
 
+// The same with a blocking copy per range and no staging.
+hipError_t read_plain(sd_ctx* c, const Piece* p, int n) {
+  hipError_t e = hipStreamSynchronize(c->stream);
+  for (int i = 0; i < n && e == hipSuccess; ++i)
+    e = hipMemcpy(p[i].dst, p[i].src, p[i].n, hipMemcpyDeviceToHost);
+  return e;
+}
+
 hipError_t read_back(sd_ctx* c, const Piece* p, int n) {
-  char* st = nullptr;
-  hipError_t e = stage_take(&st);
+  char* const st = stage_take();
+  if (!st) return read_plain(c, p, n);
+  hipError_t e = hipSuccess;
   int i0 = 0;
   while (i0 < n && e == hipSuccess) {
     // pieces [i0, i1) lie one after the other on the device
@@ -500,7 +512,7 @@ hipError_t read_back(sd_ctx* c, const Piece* p, int n) {
     i0 = i1;
   }
   if (e != hipSuccess) (void)hipStreamSynchronize(c->stream);  // nothing in flight into the halves
-  if (st) stage_give(st);
+  stage_give(st);
   return e;
 }
 
@@ -536,6 +548,8 @@ int32_t auto_block(const sd_config& c, int64_t N) {
   return (int32_t)b;
 }
 
+constexpr int32_t kMaxRing = 512;  // rows of the ring
+
 sd_status check_config(const sd_config* c, std::string* why) {
   auto bad = [&](const char* m) {
     *why = m;
@@ -551,7 +565,7 @@ sd_status check_config(const sd_config* c, std::string* why) {
   if (c->d_min < 1 || c->d_min > 31) return bad("d_min must be in [1, 31]");
   if (c->d_lo < c->d_min || c->d_hi < c->d_lo || c->d_hi > c->d_max || c->d_max > 255)
     return bad("delays must satisfy d_min <= d_lo <= d_hi <= d_max <= 255");
-  if (c->ring_len < c->d_min + c->d_max || c->ring_len > 512) return bad("ring_len out of range");
+  if (c->ring_len < c->d_min + c->d_max || c->ring_len > kMaxRing) return bad("ring_len out of range");
   if (!(c->h > 0.0) || !(c->tau_m > 0.0) || !(c->c_m > 0.0)) return bad("non-positive h/tau/C");
   if (c->model == SD_IAF_PSC_ALPHA && (!(c->tau_syn > 0.0) || c->tau_syn == c->tau_m))
     return bad("alpha model needs tau_syn > 0 and tau_syn != tau_m");
@@ -1763,17 +1777,18 @@ sd_status sd_get_stats(sd_ctx* c, sd_stats* out) {
 sd_status sd_read_ring(sd_ctx* c, float* h_out, int32_t n_slots) {
   if (!c || !h_out || n_slots < 0 || n_slots > c->cfg.ring_len) return SD_EINVAL;
   const int32_t L = c->cfg.ring_len;
-  std::vector<Piece> p;
+  Piece p[kMaxRing + 1];
+  int k = 0;
   for (int32_t s = 0; s < n_slots; ++s) {
     const int64_t t = c->t_now + s;
     float* dst = h_out + (size_t)s * c->N;
-    if (t < c->rb_hi) p.push_back({dst, c->rb + (t % L) * c->N, (size_t)c->N * 4});
+    if (t < c->rb_hi) p[k++] = {dst, c->rb + (t % L) * c->N, (size_t)c->N * 4};
     else std::memset(dst, 0, (size_t)c->N * 4);
   }
   uint32_t ended = 0;
-  if (c->watch) p.push_back({&ended, c->ended, 4});
-  if (p.empty()) HIP_TRY(c, hipStreamSynchronize(c->stream));
-  HIP_TRY(c, read_back(c, p.data(), (int)p.size()));
+  if (c->watch) p[k++] = {&ended, c->ended, 4};
+  if (k == 0) HIP_TRY(c, hipStreamSynchronize(c->stream));
+  if (k > 0) HIP_TRY(c, read_back(c, p, k));
   return not_lost(c, ended);
 }
 
@@ -1789,7 +1804,7 @@ sd_status sd_read_state(sd_ctx* c, float* h_v, float* h_y1, float* h_y2, int32_t
   uint32_t ended = 0;
   if (c->watch) p[k++] = {&ended, c->ended, 4};
   if (k == 0) HIP_TRY(c, hipStreamSynchronize(c->stream));
-  HIP_TRY(c, read_back(c, p, k));
+  if (k > 0) HIP_TRY(c, read_back(c, p, k));
   return not_lost(c, ended);
 }
 

@@ -38,3 +38,31 @@ def test_another_device_is_current():
         for h in hs:
             assert right(h), (d, L.sd_last_error(h))
     """)
+
+
+def test_no_pinned_memory():
+    """Where no pinned memory is to be had the arrays come by plain copies."""
+    run(SETUP + """
+    h = net()
+    hip.host_no_pinned(1)
+    for _ in range(8):
+        assert right(h), L.sd_last_error(h)
+    ring = np.ones((3, N), np.float32)
+    assert L.sd_read_ring(h, C.c_void_p(ring.ctypes.data), 3) == 0 and not ring.any()
+    hip.host_no_pinned(0)
+    for _ in range(8):
+        assert right(h)
+    """)
+
+
+def test_longest_ring():
+    """All rows of the longest ring at once: a list delivered as far ahead as
+    the ring allows."""
+    run("""
+    cfg = dict(W.tiny(model=0, n=40, k=5, seed=1, d_lo=4, d_hi=9), ring_len=512)
+    h = create(cfg)
+    assert L.sd_deliver_spikes(h, None, None, 0, 512 - 13) == 0
+    assert L.sd_simulate_steps(h, 8) == 0
+    ring = np.ones((512, 40), np.float32)
+    assert L.sd_read_ring(h, C.c_void_p(ring.ctypes.data), 512) == 0, L.sd_last_error(h)
+    """)
