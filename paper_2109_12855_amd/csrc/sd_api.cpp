@@ -473,6 +473,15 @@ hipError_t read_plain(sd_ctx* c, const Piece* p, int n) {
 }
 
 hipError_t read_back(sd_ctx* c, const Piece* p, int n) {
+  // a transfer queued on a stream under capture would become part of the
+  // caller's graph, into memory that is another's by its replay: the plain
+  // path's wait refuses first
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return read_plain(c, p, n);
+  }
+  if (cs != hipStreamCaptureStatusNone) return read_plain(c, p, n);
   char* const st = stage_take();
   if (!st) return read_plain(c, p, n);
   hipError_t e = hipSuccess;

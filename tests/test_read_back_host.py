@@ -66,3 +66,20 @@ def test_longest_ring():
     ring = np.ones((512, 40), np.float32)
     assert L.sd_read_ring(h, C.c_void_p(ring.ctypes.data), 512) == 0, L.sd_last_error(h)
     """)
+
+
+def test_under_capture():
+    """A read on a stream that is being captured is refused before anything of
+    it is recorded, and reads work again afterwards."""
+    run(SETUP + """
+    stream = hip.host_stream(0)
+    h = net(stream)
+    for _ in range(5):
+        assert right(h)
+    hip.host_capture(stream, 1)
+    for _ in range(2):
+        assert read(h, N)[0] == -3  # SD_EHIP
+    assert hip.host_recorded() == 0
+    hip.host_capture(stream, 0)
+    assert right(h)
+    """)
