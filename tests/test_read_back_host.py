@@ -83,3 +83,25 @@ def test_under_capture():
     hip.host_capture(stream, 0)
     assert right(h)
     """)
+
+
+def test_pinned_memory_where_it_pays():
+    """A program that reads a small net a few times takes no pinned memory, one
+    that goes on takes it once; a large net's first read does."""
+    run(SETUP + """
+    small = W.tiny(model=1, n=1250, k=5, seed=1, d_lo=4, d_hi=9)
+    h = create(small, build=False)
+    for _ in range(3):
+        assert read(h, 1250)[0] == 0
+    assert hip.host_pinned() == 0
+    for _ in range(50):
+        assert read(h, 1250)[0] == 0
+    assert hip.host_pinned() == 1
+    """)
+    run(SETUP + """
+    cfg["n_exc"] = 8 * N - cfg["n_inh"]  # 16 MiB of state
+    h = create(cfg, build=False)
+    for _ in range(3):
+        assert read(h, 8 * N)[0] == 0
+        assert hip.host_pinned() == 1
+    """)
