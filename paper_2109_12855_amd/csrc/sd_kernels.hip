@@ -2128,6 +2128,7 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
   int64_t chunk_done = (t0 >> 3) - 1;      // chunks drawn so far (dring)
   int db = dring ? (int)(t0 % drows) : 0;  // drive-count row of step w_lo
 
+  const float inv_nb = 1.0f / (float)nb;
   // Philox drive counts of the steps [w, w + Dmin), w's row wrow: one block
   // per (neuron, 8-step chunk), shared out over n threads of index i0; a chunk
   // that reaches past the slice is kept for the next one (dring) or drawn
@@ -2135,15 +2136,13 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
   auto drive = [&](int64_t w, int wrow, int i0, int n) {
     const int64_t c1 = (w + Dmin - 1) >> 3;
     const int64_t c0 = dring ? chunk_done + 1 : w >> 3;
-    const int n_ch = (int)(c1 - c0 + 1), row0 = wrow + (int)(c0 * 8 - w);
+    const int n_tasks = (int)(c1 - c0 + 1) * nb, row0 = wrow + (int)(c0 * 8 - w);
     chunk_done = c1;
-    int dn = i0, ci = 0;
-    for (;;) {
-      while (dn >= nb) {
-        dn -= nb;
-        ++ci;
-      }
-      if (ci >= n_ch) break;
+    for (int task = i0; task < n_tasks; task += n) {
+      // task / nb as in the slice kernel (counted down by nb, a last block of 4
+      // neurons took 240 rounds: 2,500 delta neurons 11.9 -> 7.1 us per slice)
+      const int ci = (int)(((float)task + 0.5f) * inv_nb);
+      const int dn = task - ci * nb;
       uint64_t rr[4];
       uint32_t cnt[8];
       philox(a.seed, STREAM_DRIVE, (uint64_t)(j0 + dn), (uint64_t)(c0 + ci), rr);
@@ -2154,7 +2153,6 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
 #pragma unroll
       for (int q = 0; q < 8; ++q)
         if (dring || (row + q >= 0 && row + q < Dmin)) dcnt[(row + q) * B + dn] = (uint8_t)cnt[q];
-      dn += n;
     }
   };
 
