@@ -246,8 +246,10 @@ sd_status sd_set_count_mode(sd_ctx* ctx, int32_t on);
  * neurons' state on its compute unit across the slices; between slices the
  * blocks exchange their spikes through device memory.  The results are those
  * of the fused slices bit for bit.  A new context runs stretches of 4 and
- * more slices this way by itself where the net allows it (and the stream is
- * not being captured); 0 switches to one launch per slice.
+ * more slices this way by itself where the net allows it, the stream is not
+ * being captured and, for a net of at most half the compute units, such nets
+ * of the device live on at most two streams (their persistent launches would
+ * queue one behind another); 0 switches to one launch per slice.
  * SD_EUNSUPPORTED unless the net is block-major, closed loop, with
  * static synapses, blocks of a multiple of 64 and at most 1024 neurons, and
  * all blocks fit on the device at once; SD_ESTATE before

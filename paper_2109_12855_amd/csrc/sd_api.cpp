@@ -315,6 +315,10 @@ struct sd_ctx {
   uint32_t* ended = nullptr;
   uint32_t persist_n = 0;   // persistent launches so far (their serials)
   bool watch = false, lost = false;
+  // nets that could run persistent slices beside each other: a list through
+  // the contexts
+  bool beside = false;
+  sd_ctx *beside_prev = nullptr, *beside_next = nullptr;
 };
 
 // Independent networks advanced together: every slice of all members is
@@ -539,6 +543,63 @@ hipError_t read_back(sd_ctx* c, const Piece* p, int n) {
   return e;
 }
 
+bool open_loop(const sd_config& c) { return c.n_src_exc > 0; }
+
+// Nets whose slices the persistent kernel can run.
+bool persist_kind(const sd_ctx* c) {
+  return !c->sm && !c->cfg.plastic && !open_loop(c->cfg) && c->B <= kSliceThreads &&
+         c->B % 64 == 0;
+}
+
+// Live contexts whose launches leave room beside them: closed-loop block-major
+// nets of at most half the compute units.  Cooperative launches queue one
+// behind another; in launches of one slice such nets run side by side on
+// streams of their own.  us per slice of all nets, persistent / one launch per
+// slice, stretches of 20 slices on 3, 4, 6 and 8 streams:
+//   1,250 delta neurons  27.7 / 11.9  36.8 / 23.0  56.9 / 23.1  79.6 / 34.2
+//   2,500 alpha neurons  29.3 / 13.7  39.5 / 26.0  59.6 / 26.4  81.0 / 38.9
+//   8,000 alpha neurons  30.9 / 17.5  41.0 / 30.6  61.8 / 35.8  84.9 / 53.0
+// and on 2 streams 14.6 / 15.8, 15.4 / 17.4, 16.7 / 18.5.  So from
+// kBesideStreams streams on they do without, whether or not all are busy: a
+// stream is not asked, it may be its owner's to capture.  Nets of 188 blocks
+// gain on any number of streams (8 of them 72 / 87).
+constexpr int kBesideStreams = 3;
+struct Beside {
+  std::mutex m;
+  sd_ctx* head = nullptr;
+};
+Beside& beside() {
+  static Beside b;
+  return b;
+}
+void beside_add(sd_ctx* c) {
+  Beside& b = beside();
+  std::lock_guard<std::mutex> lock(b.m);
+  c->beside = true;
+  c->beside_next = b.head;
+  if (b.head) b.head->beside_prev = c;
+  b.head = c;
+}
+void beside_remove(sd_ctx* c) {
+  if (!c->beside) return;
+  Beside& b = beside();
+  std::lock_guard<std::mutex> lock(b.m);
+  (c->beside_prev ? c->beside_prev->beside_next : b.head) = c->beside_next;
+  if (c->beside_next) c->beside_next->beside_prev = c->beside_prev;
+}
+// Streams of such contexts of c's device, c's own among them, up to
+// kBesideStreams.
+int beside_streams(const sd_ctx* c) {
+  Beside& b = beside();
+  std::lock_guard<std::mutex> lock(b.m);
+  hipStream_t seen[kBesideStreams] = {c->stream};
+  int n = 1;
+  for (const sd_ctx* x = b.head; x && n < kBesideStreams; x = x->beside_next)
+    if (x->device == c->device && std::find(seen, seen + n, x->stream) == seen + n)
+      seen[n++] = x->stream;
+  return n;
+}
+
 // SD_OK unless a persistent launch that nobody asked for ended early.
 sd_status not_lost(sd_ctx* c) {
   return c->lost ? fail(c, SD_EOVERFLOW, "a persistent launch ended early (a wait for other "
@@ -559,8 +620,6 @@ sd_status sync_not_lost(sd_ctx* c) {
   if (c->watch) HIP_TRY(c, hipMemcpy(&ended, c->ended, 4, hipMemcpyDeviceToHost));
   return not_lost(c, ended);
 }
-
-bool open_loop(const sd_config& c) { return c.n_src_exc > 0; }
 
 int32_t auto_block(const sd_config& c, int64_t N) {
   if (c.block_neurons > 0) return c.block_neurons;
@@ -1255,6 +1314,9 @@ sd_status sd_create(const sd_config* cfg, void* hip_stream, void* d_arena, size_
   c->lau.lds = lds;
   c->lau.wform = g.wform;
   c->lau.single_nb = c->NB;
+  int n_cu = 0;
+  HIP_TRY(c, hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, c->device));
+  if (persist_kind(c) && 2 * c->NB <= n_cu) beside_add(c);
   return SD_OK;
 }
 
@@ -1266,6 +1328,7 @@ void sd_destroy(sd_ctx* c) {
   if (c->in_off) (void)hipFree(c->in_off);
   if (c->in_cnt) (void)hipFree(c->in_cnt);
   launcher_free(c->lau);
+  beside_remove(c);
   delete c;
   stage_user(-1);
 }
@@ -1564,11 +1627,6 @@ sd_status persist_fits(sd_ctx* c, bool* fits, int* occ_out = nullptr, int* n_cu_
   return SD_OK;
 }
 
-bool persist_kind(const sd_ctx* c) {
-  return !c->sm && !c->cfg.plastic && !open_loop(c->cfg) && c->B <= kSliceThreads &&
-         c->B % 64 == 0;
-}
-
 // Slices the next launch runs persistently from an aligned t_now with left
 // steps to go (0: one launch per slice).
 sd_status persist_slices(sd_ctx* c, int64_t left, int32_t* S) {
@@ -1592,6 +1650,7 @@ sd_status persist_slices(sd_ctx* c, int64_t left, int32_t* S) {
       return SD_OK;
     }
     if (cs != hipStreamCaptureStatusNone) return SD_OK;
+    if (c->beside && beside_streams(c) >= kBesideStreams) return SD_OK;
     bool fits = false;
     sd_status s = persist_fits(c, &fits);
     if (s != SD_OK || !fits) return s;
