@@ -928,13 +928,15 @@ sd_status launch_slice_checked(sd_ctx* c, const SliceArgs& a) {
 }
 
 // Lanes per segment of the block-major walk: the fewest that hold a segment of
-// mean length m = K B / N and two standard deviations (Poisson) more; with 64,
+// mean length m = K B / n_src and two standard deviations (Poisson) more; with 64,
 // a segment of 6 to 22 synapses leaves most of a wave idle.  20 slices of
 // 30,011 neurons (m = 12.8): 304 us with 64 lanes, 252 with 32, 273 with 16,
 // where a fifth of the segments take a second round; 100 slices of 1,250
-// neurons (m = 6.4): 768 us with 64, 674 with 16.
+// neurons (m = 6.4): 768 us with 64, 674 with 16.  Open loop, N != n_src:
+// 60,000 neurons of 600,000 sources (m = 2.6) 76 us per slice with 64 lanes,
+// 45.5 with 16; 30,011 of 6,000 (m = 64) 20.7 with 32, 19.4 with 64.
 int32_t walk_lanes(const sd_ctx* c) {
-  const double m = (double)c->K * c->B / (double)c->N;
+  const double m = (double)c->K * c->B / (double)c->n_src;
   const double top = m + 2.0 * std::sqrt(m);
   return top <= 16.0 ? 16 : top <= 32.0 ? 32 : 64;
 }
