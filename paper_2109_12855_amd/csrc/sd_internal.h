@@ -251,7 +251,10 @@ struct PersistArgs {
   uint32_t serial;     // this launch; kPersistUnasked: nobody asked for it
 };
 constexpr uint32_t kPersistUnasked = 0x80000000u;
-constexpr int kPersistMaxNB = 512;  // two 1024-thread workgroups per compute unit
+// Blocks of a persistent launch: all are resident, and the kernel's registers
+// (over 64 per thread) let a compute unit hold one of its 1024-thread
+// workgroups, of 256 on the device.
+constexpr int kPersistMaxNB = 256;
 bool persist_plan(int32_t B, int32_t Dmin, int32_t Dmax, size_t budget, PersistPlan* plan);
 size_t xch_bytes(int32_t NB);  // exchange lines of NB blocks
 int persist_occupancy(int wform, const PersistPlan& plan);

@@ -2200,7 +2200,7 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
     return true;
   };
 
-  int wbase[kPersistMaxNB / 256] = {};  // this wave's first list positions
+  int wbase = 0;  // this wave's first list position
   int cur = pp->cur0;
   bool ok = true;
   __syncthreads();  // window, thresholds, counters
@@ -2222,13 +2222,13 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
       if (k > 0) {
         // Spikes of every block's line, as descriptors of the positions [c0,
         // c0 + CAP); the first round waits for the lines and counts the
-        // spikes into s_tot.  16 lines per wave, words 0..3 one per lane.
+        // spikes into s_tot.  16 lines per wave (kPersistMaxNB in all), words
+        // 0..3 one per lane.
         const uint32_t tag_in = (tag - 1u) & 0xffffu;
         const uint64_t* xin = pp->xch + (size_t)(tag_in & 1u) * NB * kXchWords;
         if (pp->spin_limit == 0) give_up(1);  // no polls allowed
-        int gi = 0;
-#pragma unroll 1
-        for (int g = wv * 16; g < NB; g += nwv * 16, ++gi) {
+        const int g = wv * 16;
+        if (g < NB) do {
           const int blk = g + (lane >> 2), kw = lane & 3;
           const bool has = blk < NB;
           const uint64_t* line = xin + (size_t)(has ? blk : 0) * kXchWords;
@@ -2256,11 +2256,9 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
             if (lane == 0 && tot)
               w0 = __hip_atomic_fetch_add(&s_tot, tot, __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-            w0 = __builtin_amdgcn_readfirstlane(w0);
-            if (gi == 0) wbase[0] = w0;
-            else wbase[1] = w0;
+            wbase = __builtin_amdgcn_readfirstlane(w0);
           }
-          const int base = (gi == 0 ? wbase[0] : wbase[1]) - (int)c0 + pre;
+          const int base = wbase - (int)c0 + pre;
           const int first = kw == 0 ? 0 : 3 * kw - 1;
           put_word(w, blk, first, kw == 0 ? 2 : 3, cnt, base + first);
           // the other words of lines with more spikes: two lines at a time,
@@ -2320,7 +2318,7 @@ __global__ void __launch_bounds__(kSliceThreads) k_persist(PersistArgs p) {
               }
             }
           }
-        }
+        } while (false);
       } else {
         for (int64_t i = c0 + tid; i < total && i < c0 + CAP; i += kSliceThreads) {
           const uint32_t ent = ilist[i];
