@@ -2026,14 +2026,15 @@ __host__ __device__ inline PersistLds persist_lds_layout(int B, int Dmax, int dr
 // without a neuron draw the next slice's drive while the others update, which
 // needs drive rows of two slices and pays from six such waves (blocks of at
 // most 640 neurons: with fewer the update waits for them).  Then carry rows
-// in LDS before the HBM ring, and drive counts kept for whole 8-step chunks
-// before drawn again per slice.  Walk chunks take what is left, at most 2048
-// spikes.
+// in LDS before the HBM ring, and last drive counts drawn again per slice
+// instead of kept for whole 8-step chunks (17 of the 20,055 geometries that the
+// block-major layout takes, 1024 neurons with delays of 2 to 18 steps one of
+// them).  Walk chunks take what is left, at most 2048 spikes.
 bool persist_plan(int32_t B, int32_t Dmin, int32_t Dmax, size_t budget, PersistPlan* plan) {
-  for (int k = B <= kSliceThreads - 6 * 64 ? 0 : 1; k < 5; ++k) {
+  for (int k = B <= kSliceThreads - 6 * 64 ? 0 : 1; k < 4; ++k) {
     PersistPlan p;
     p.helpers = k == 0;
-    p.carry_lds = k == 0 || k == 1 || k == 3;
+    p.carry_lds = k < 2;
     p.drows = k == 0 ? (2 * Dmin + 14) / 8 * 8 : k < 3 ? (Dmin + 14) / 8 * 8 : Dmin;
     p.crows = p.carry_lds ? Dmax - Dmin : 0;
     const size_t base = persist_lds_layout(B, Dmax, p.drows, p.crows, 0).total;
