@@ -614,6 +614,13 @@ sd_status not_lost(sd_ctx* c, uint32_t ended) {
   c->watch = false;
   return not_lost(c);
 }
+// ... and with the overflow flags, which every early end sets too.
+sd_status not_lost_flags(sd_ctx* c, int32_t overflow) {
+  uint32_t ended = 0;
+  if (c->watch && (overflow & 16))
+    HIP_TRY(c, hipMemcpy(&ended, c->ended, 4, hipMemcpyDeviceToHost));
+  return not_lost(c, ended);
+}
 sd_status sync_not_lost(sd_ctx* c) {
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   uint32_t ended = 0;
@@ -887,7 +894,7 @@ sd_status make_layout(const sd_config* c, Layout* L, std::string* why) {
   L->off_p64 = take(8 * 8);
   L->off_p32 = take(8 * 4);
   L->off_counters = take(8 * 8);
-  L->off_overflow = take(4);
+  L->off_overflow = take(4);  // within 512 bytes of the counters (sd_get_spikes)
   L->off_xch = take(L->sm || c->plastic ? 0 : xch_bytes(L->NB));
   const size_t brec = c->wform == SD_W_FP32 ? 8 : 4;
   L->off_bins = take(L->sm ? (size_t)L->NB * L->bin_P * L->bin_cap * brec : 0);
@@ -1843,10 +1850,11 @@ sd_status sd_get_stats(sd_ctx* c, sd_stats* out) {
   if (!c || !out) return SD_EINVAL;
   unsigned long long cnt[4];
   int32_t ov = 0;
-  const sd_status s = sync_not_lost(c);
-  if (s != SD_OK && s != SD_EOVERFLOW) return s;
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
   HIP_TRY(c, hipMemcpy(cnt, c->counters, sizeof cnt, hipMemcpyDeviceToHost));
   HIP_TRY(c, hipMemcpy(&ov, c->overflow, 4, hipMemcpyDeviceToHost));
+  const sd_status s = not_lost_flags(c, ov);
+  if (s != SD_OK && s != SD_EOVERFLOW) return s;
   out->t_now = c->t_now;
   out->events_delivered = (int64_t)cnt[0];
   out->spikes_delivered = (int64_t)cnt[1];
@@ -2044,9 +2052,16 @@ sd_status sd_get_spikes(sd_ctx* c, int64_t* h_step, uint32_t* h_id, int64_t cap,
   if (!c || !n) return SD_EINVAL;
   *n = 0;
   if (c->rec_cap == 0) return fail(c, SD_ESTATE, "spike recording is off");
-  if (sd_status s = sync_not_lost(c)) return s;
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  // the counters and, in the arena's next line, the overflow flags
+  unsigned char raw[512];
+  const size_t ov_at = (size_t)((char*)c->overflow - (char*)c->counters);
+  HIP_TRY(c, hipMemcpy(raw, c->counters, ov_at + 4, hipMemcpyDeviceToHost));
+  int32_t ov = 0;
+  std::memcpy(&ov, raw + ov_at, 4);
+  if (sd_status s = not_lost_flags(c, ov)) return s;
   unsigned long long total = 0;
-  HIP_TRY(c, hipMemcpy(&total, c->counters + 3, 8, hipMemcpyDeviceToHost));
+  std::memcpy(&total, raw + 3 * 8, 8);
   const int64_t avail = std::min<int64_t>((int64_t)total, c->rec_cap) - c->rec_read;
   const int64_t m = std::min<int64_t>(avail, cap);
   if (m > 0) {
@@ -2068,9 +2083,11 @@ sd_status sd_get_pending(sd_ctx* c, uint32_t* h_src, uint8_t* h_lag, int64_t cap
   *n = 0;
   if (slice_t0) *slice_t0 = c->pend_open ? c->pend_t0 : -1;
   if (!c->pend_open || open_loop(c->cfg)) return SD_OK;
-  if (sd_status s = sync_not_lost(c)) return s;
-  int32_t cnt = 0;
-  HIP_TRY(c, hipMemcpy(&cnt, c->cnt3 + c->ci, 4, hipMemcpyDeviceToHost));
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  uint32_t block[kCntWord + 3];  // the word of an early end and the list counters
+  HIP_TRY(c, hipMemcpy(block, c->ended, sizeof block, hipMemcpyDeviceToHost));
+  if (sd_status s = not_lost(c, block[0])) return s;
+  const int32_t cnt = (int32_t)block[kCntWord + (size_t)c->ci];
   const int64_t nl = std::min<int64_t>(cnt, c->list_cap);
   std::vector<uint32_t> all((size_t)nl);
   if (nl > 0)

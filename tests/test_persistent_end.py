@@ -16,19 +16,20 @@ SETUP = """
     saved = C.create_string_buffer(n.value)
     assert L.sd_save_state(h, saved, n.value, C.byref(n)) == 0
 
+    ring = np.zeros((4, 100), np.float32)
+    st = sdeliver.sd_stats()
+    m, t0 = C.c_int64(), C.c_int64()
+    READS = dict(
+        state=lambda: read(h, 100)[0],
+        none=lambda: L.sd_read_state(h, None, None, None, None),
+        ring=lambda: L.sd_read_ring(h, C.c_void_p(ring.ctypes.data), 4),
+        spikes=lambda: L.sd_get_spikes(h, None, None, 0, C.byref(m)),
+        pending=lambda: L.sd_get_pending(h, None, None, 0, C.byref(m), C.byref(t0)),
+        save=lambda: L.sd_save_state(h, None, 0, C.byref(n)),
+        stats=lambda: L.sd_get_stats(h, C.byref(st)))
+
     def calls():
-        ring = np.zeros((4, 100), np.float32)
-        st = sdeliver.sd_stats()
-        m, t0 = C.c_int64(), C.c_int64()
-        return dict(
-            state=read(h, 100)[0],
-            none=L.sd_read_state(h, None, None, None, None),
-            ring=L.sd_read_ring(h, C.c_void_p(ring.ctypes.data), 4),
-            spikes=L.sd_get_spikes(h, None, None, 0, C.byref(m)),
-            pending=L.sd_get_pending(h, None, None, 0, C.byref(m), C.byref(t0)),
-            save=L.sd_save_state(h, None, 0, C.byref(n)),
-            stats=L.sd_get_stats(h, C.byref(st)))
-    FIRST = ["state", "none", "ring", "spikes", "pending", "save", "stats"]
+        return {k: f() for k, f in READS.items()}
 """
 
 
@@ -37,13 +38,12 @@ def test_unasked_launch():
     assert L.sd_simulate_steps(h, 8 * D) == 0
     assert (launches()[:, 0] == 1).all()
     assert set(calls().values()) == {0}
-    for first in range(7):  # whichever call looks first
+    for first in READS:  # whichever call looks first
         hip.host_end_early(1)
         assert L.sd_simulate_steps(h, 8 * D) == 0
         hip.host_end_early(0)
         assert L.sd_simulate_steps(h, 8 * D) == 0  # queued before anybody looked
-        if first == 0: assert read(h, 100)[0] == OVERFLOW
-        if first == 3: assert L.sd_get_spikes(h, None, None, 0, C.byref(C.c_int64())) == OVERFLOW
+        assert READS[first]() == OVERFLOW, first
         got = calls()
         assert set(got.values()) == {OVERFLOW}, got
         assert b"ended early" in L.sd_last_error(h)
