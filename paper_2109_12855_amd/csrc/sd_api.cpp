@@ -295,7 +295,9 @@ struct sd_ctx {
   int cur = 0;              // list buffer holding the open slice
   int32_t count_mode = 0;
   int64_t slices = 0;
-  int64_t rec_read = 0;     // raster entries already drained
+  int64_t rec_read = 0;     // raster entries already drained or held
+  std::vector<uint2> rec_held;  // in slice order (nets that ran persistent slices)
+  size_t rec_at = 0;        // of them already drained
   SliceLauncher lau;        // this network alone
   // slices per persistent launch (kPersistAuto: where it pays, 0: one launch
   // per slice)
@@ -1976,7 +1978,7 @@ sd_status sd_save_state(sd_ctx* c, void* h_buf, size_t cap, size_t* used) {
   hd.pend_t0 = c->pend_t0;
   hd.slices = c->slices;
   hd.n_pending = n_pend;
-  hd.rec_read = c->rec_read;
+  hd.rec_read = c->rec_read - (int64_t)(c->rec_held.size() - c->rec_at);
   hd.L = L;
   hd.pend_open = c->pend_open ? 1 : 0;
   hd.count_mode = c->count_mode;
@@ -2042,6 +2044,8 @@ sd_status sd_load_state(sd_ctx* c, const void* h_buf, size_t n) {
   c->slices = hd.slices;
   c->count_mode = hd.count_mode;
   c->rec_read = 0;
+  c->rec_held.clear();
+  c->rec_at = 0;
   const uint32_t none = 0;
   HIP_TRY(c, hipMemcpy(c->ended, &none, 4, hipMemcpyHostToDevice));
   c->watch = c->lost = false;
@@ -2063,17 +2067,52 @@ sd_status sd_get_spikes(sd_ctx* c, int64_t* h_step, uint32_t* h_id, int64_t cap,
   unsigned long long total = 0;
   std::memcpy(&total, raw + 3 * 8, 8);
   const int64_t avail = std::min<int64_t>((int64_t)total, c->rec_cap) - c->rec_read;
-  const int64_t m = std::min<int64_t>(avail, cap);
-  if (m > 0) {
-    std::vector<uint2> buf((size_t)m);
-    HIP_TRY(c, hipMemcpy(buf.data(), c->rec + c->rec_read, (size_t)m * 8, hipMemcpyDeviceToHost));
-    for (int64_t i = 0; i < m; ++i) {
-      if (h_step) h_step[i] = buf[i].x;
-      if (h_id) h_id[i] = buf[i].y;
-    }
-    c->rec_read += m;
+  // Blocks of a persistent launch record a slice's spikes after they published
+  // them, so nothing but time keeps another block's next slice behind: such
+  // rasters are taken whole and put in slice order here (a stream that is waited
+  // for holds no slice in part).
+  const bool held = c->persist_n > 0;
+  if (held && avail > 0) {
+    std::vector<uint2>& r = c->rec_held;
+    r.erase(r.begin(), r.begin() + (std::ptrdiff_t)c->rec_at);
+    c->rec_at = 0;
+    const size_t at = r.size();
+    r.resize(at + (size_t)avail);
+    const hipError_t e = hipMemcpy(r.data() + at, c->rec + c->rec_read, (size_t)avail * 8,
+                                   hipMemcpyDeviceToHost);
+    if (e != hipSuccess) r.resize(at);
+    HIP_TRY(c, e);
+    c->rec_read += avail;
+    const uint32_t D = (uint32_t)c->cfg.d_min;
+    auto before = [D](const uint2& x, const uint2& y) { return x.x / D < y.x / D; };
+    const auto b = r.begin() + (std::ptrdiff_t)at;
+    if (!std::is_sorted(b, r.end(), before)) std::stable_sort(b, r.end(), before);
   }
-  *n = std::max<int64_t>(m, 0);
+  const int64_t left = held ? (int64_t)(c->rec_held.size() - c->rec_at) : avail;
+  const int64_t m = std::max<int64_t>(std::min<int64_t>(left, cap), 0);
+  if (m > 0) {
+    std::vector<uint2> buf;
+    const uint2* from = nullptr;
+    if (held) {
+      from = c->rec_held.data() + c->rec_at;
+      c->rec_at += (size_t)m;
+    } else {
+      buf.resize((size_t)m);
+      HIP_TRY(c, hipMemcpy(buf.data(), c->rec + c->rec_read, (size_t)m * 8,
+                           hipMemcpyDeviceToHost));
+      c->rec_read += m;
+      from = buf.data();
+    }
+    for (int64_t i = 0; i < m; ++i) {
+      if (h_step) h_step[i] = from[i].x;
+      if (h_id) h_id[i] = from[i].y;
+    }
+  }
+  if (held && c->rec_at == c->rec_held.size()) {
+    std::vector<uint2>().swap(c->rec_held);
+    c->rec_at = 0;
+  }
+  *n = m;
   return (int64_t)total > c->rec_cap ? SD_EOVERFLOW : SD_OK;
 }
 

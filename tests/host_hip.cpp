@@ -24,7 +24,7 @@ std::map<const void*, std::string> names;
 std::vector<Launch> launches;
 Stream null_stream{0, false};
 int device = 0;
-bool no_pinned = false, end_early = false;
+bool no_pinned = false, end_early = false, record = false;
 int64_t n_pinned = 0, n_recorded = 0;
 struct { dim3 grid, block; size_t lds; hipStream_t s; } config;
 
@@ -45,6 +45,15 @@ void note(const void* fn, void** args, hipStream_t s) {
       *p->ended = p->serial;
       *p->a.overflow |= 16;
     }
+    // two blocks' rasters as a slow second block leaves them: its spikes of a
+    // slice (neuron 64) after the first block's of the next one (neuron 0)
+    if (record)
+      for (int k = 0; k <= p->S; ++k)
+        for (int b = 0; b < 2; ++b) {
+          if (k - b < 0 || k - b >= p->S) continue;
+          const int64_t t = p->t0 + (int64_t)(k - b) * p->a.Dmin;
+          p->a.rec[(*p->a.rec_n)++] = make_uint2((uint32_t)t, 64u * b);
+        }
   } else if (is(n, "k_slice1")) {
     const auto* a = (const sd::SliceArgs*)args[0];
     l.f[0] = 2;
@@ -68,6 +77,7 @@ void host_launch(int64_t i, int64_t* out) { std::memcpy(out, launches[(size_t)i]
 void host_clear() { launches.clear(); }
 void host_no_pinned(int on) { no_pinned = on; }
 void host_end_early(int on) { end_early = on; }  // persistent launches to come
+void host_record(int on) { record = on; }
 int64_t host_pinned() { return n_pinned; }
 int64_t host_recorded() { return n_recorded; }
 void host_capture(void* s, int on) { of((hipStream_t)s)->capturing = on; }
