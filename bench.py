@@ -11,7 +11,7 @@ alpha-current neurons at in-degree 11,250 drawn from a virtual population of
 open loop, 1 ms slices.  A slice is two launches on the context's stream
 (the binning pass and the fused accumulate/update kernel); ``value`` is
 synaptic events per second over the timed slices, the roofline fraction is
-algorithmic bytes per slice (5 B per synapse for the BF16 forms) over the
+bytes per slice (5 B per synapse here, as a delivery reads them) over the
 measured time per slice, against 8 TB/s.
 
 Also reported: the same share in the FP32 form, the 112,500-neuron closed-
@@ -44,7 +44,8 @@ SHARE_TRAFFIC = os.path.join(PROFILES, "k_bin_k_slice1_alpha_share_1125000_bf16_
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2109_12855_amd", "csrc", f)
                   for f in ("sd_kernels.hip", "sd_internal.h")]
 SETTLE_SLICES = 200          # untimed biological settle of the closed-loop net (200 ms)
-B_SYN = {0: 9, 1: 5, 2: 5, 3: 4}   # algorithmic bytes per synapse of each storage form
+# bytes a delivery reads per synapse, by layout and storage form
+B_SYN = {"block_major": {0: 6, 1: 4, 2: 4, 3: 4}, "source_major": {0: 8, 1: 5, 2: 5}}
 
 
 def kernel_source_hash() -> str:
@@ -126,10 +127,10 @@ def algorithmic_bytes(events: float, spikes: float, n: int, d_min: int, b_syn: i
     return events * b_syn + n * d_min * 8 + n * 2 * s_state + spikes * b_spike
 
 
-# Plastic synapses (FP32 form): each event reads its 9-byte record and writes
-# its 4-byte weight back; each neuron's state adds a 12-byte spike history;
+# Plastic synapses (FP32 form): each event reads its weight and slot (6 bytes)
+# and writes its 4-byte weight back; each neuron's state adds a 12-byte spike history;
 # each spike-list entry adds a lag mask and the source's previous spike.
-PLASTIC_B_EVENT, PLASTIC_S_STATE, PLASTIC_B_SPIKE = 13, 16 + 12, 13
+PLASTIC_B_EVENT, PLASTIC_S_STATE, PLASTIC_B_SPIKE = 6 + 4, 16 + 12, 13
 
 
 def _free(obj):
@@ -174,7 +175,8 @@ def time_net(cfg: dict, steps: int, warmup: int, settle: int = 0, open_loop: boo
     emitted = s1["spikes_emitted"] - s0["spikes_emitted"]
     slices = s1["slices"] - s0["slices"]
     n = net.n_local
-    b_syn = B_SYN[cfg["wform"]]
+    layout = "source_major" if net.sizes["layout"] == 2 else "block_major"
+    b_syn = B_SYN[layout][cfg["wform"]]
     s_state = 16 if cfg["model"] == 1 else 8
     b_spk = 5
     if cfg.get("plastic"):
@@ -182,7 +184,7 @@ def time_net(cfg: dict, steps: int, warmup: int, settle: int = 0, open_loop: boo
     b_alg = algorithmic_bytes(ev / slices, spk / slices, n, d_min, b_syn, s_state, b_spk)
     us = ms * 1e3 / slices
     out = dict(name=cfg["name"], synapses=net.n_syn, build_s=round(t_build, 2),
-               layout="source_major" if net.sizes["layout"] == 2 else "block_major",
+               layout=layout,
                block_neurons=net.sizes["block_neurons"], bin_cap=net.sizes["bin_cap"],
                stored_bytes_per_synapse=net.sizes["bytes_per_synapse"],
                alg_bytes_per_synapse=b_syn, slices=slices, ms_total=ms, us_per_slice=us,
@@ -284,7 +286,7 @@ def sweep(slices: int = 120, warmup: int = 20) -> dict:
         for m, x, y, c in zip(bt.members, st0, st1, cfgs):
             b_alg += algorithmic_bytes((y["events_delivered"] - x["events_delivered"]) / slices,
                                        (y["spikes_delivered"] - x["spikes_delivered"]) / slices,
-                                       m.n_local, d_min, B_SYN[wform], 8)
+                                       m.n_local, d_min, B_SYN["block_major"][wform], 8)
         us = ms * 1e3 / slices
         out[key] = {"synapses": int(sum(m.n_syn for m in bt.members)),
                     "blocks": int(sum(m.sizes["n_blocks"] for m in bt.members)),

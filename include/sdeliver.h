@@ -51,18 +51,19 @@ typedef enum {
 
 typedef enum { SD_IAF_PSC_DELTA = 0, SD_IAF_PSC_ALPHA = 1 } sd_model;
 
-/* Storage form of a synapse (weight, target, delay); the slot is its place in
- * the target block's ring window, (delay - d_min) * block_neurons + offset in
- * block:
- *   SD_W_FP32        f32 weight, u16 slot and u8 delay - d_min in one 32-bit
- *                    word, u8 delay (exports)                   (9 B / synapse)
- *   SD_W_BF16        bf16 weight, u16 slot, u8 delay (exports)  (5 B)
+/* Storage form of a synapse (weight, target, delay).  Block-major a synapse is
+ * a weight and a slot, its place in the target block's ring window,
+ * (delay - d_min) * block_neurons + offset in block, and a delivery reads both:
+ *   SD_W_FP32        f32 weight; the u16 slots in an array of
+ *                    their own                                   (6 B / synapse)
+ *   SD_W_BF16        bf16 weight and u16 slot in one u32         (4 B)
  *   SD_W_BF16_RESID  bf16 residual d, w = mu_pop * (1 + d), where mu_pop is
- *                    the FP32 mean weight of the source's population,
- *                    u16 slot, u8 delay (exports)               (5 B)
- *   SD_W_BF16_PACKED the residual weight and the slot           (4 B);
+ *                    the FP32 mean weight of the source's population, and
+ *                    u16 slot in one u32                         (4 B)
+ *   SD_W_BF16_PACKED the same record                             (4 B);
  *                    needs (d_max - d_min + 1) * block_neurons <= 65536
- * A delivery reads 8 bytes per event in the FP32 form and 4 in the others.
+ * The arena (and sd_sizes) hold 9, 5, 5 and 4 bytes per synapse for them: the
+ * rest is not written or read.
  * In the source-major layout the targets are cut into parts of 2^tbits
  * (tbits = 24 - the bits of d_max - d_min, at most 4 parts) and each source
  * has one segment per part.  A record is a u32 {offset in the part (tbits),
@@ -149,8 +150,9 @@ typedef struct {
   int32_t n_blocks;          /* number of target blocks                         */
   int64_t table_bytes;       /* synapse arrays + segment pointers               */
   int64_t arena_bytes;       /* total device memory of a context                */
-  int32_t bytes_per_synapse; /* block-major: 9 (FP32), 5 (BF16, residual), 4
-                                (packed); source-major: 8 (FP32), 5 (BF16s)   */
+  int32_t bytes_per_synapse; /* held in the table.  block-major: 9 (FP32), 5
+                                (BF16, residual), 4 (packed); source-major:
+                                8 (FP32), 5 (BF16s)                           */
   int32_t layout;            /* the layout in use (SD_LAYOUT_BLOCK / _SOURCE)   */
   int32_t bin_cap;           /* source-major: binned records per region in use
                                 (the configured or automatic bin_cap); 0 for

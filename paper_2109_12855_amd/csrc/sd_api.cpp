@@ -356,8 +356,9 @@ namespace {
 // networks differ several times in work per block (in-degree and rate) and a
 // busy one kept on one XCD holds up the launch: 16 sweep nets took 320 us per
 // slice with whole networks per XCD, of which the other seven idled through
-// half.  Blocks that take more synapses per spike rate go first, so that the
-// last to start are short.
+// half.  Nets of more synapses per block (in-degree times block size) go first,
+// so that the last blocks to start are short; their rates, which move during a
+// run, are not known here.
 std::vector<int2> xcd_map(const std::vector<sd_ctx*>& nets) {
   std::vector<int32_t> order(nets.size());
   for (size_t i = 0; i < nets.size(); ++i) order[i] = (int32_t)i;
@@ -874,9 +875,9 @@ sd_status make_layout(const sd_config* c, Layout* L, std::string* why) {
   L->off_cursor = take((size_t)L->M * ptr);
   L->off_seg = take(L->sm ? 0 : (size_t)L->n_src * L->NB * 8);
   L->off_tiles = take((size_t)L->n_tiles * ptr);
-  // record 0 always readable; the FP32 form fills 6 of its 8 bytes per synapse,
-  // and no block-major form the byte of a delay (every slot holds it): the sizes
-  // that callers see stay as they are
+  // record 0 always readable; of the block-major forms FP32 fills 6 of its 8
+  // bytes per synapse, and none the byte of a delay (every slot holds it): the
+  // sizes that sd_query_sizes reports, and so the arena, keep them
   L->off_syn = take(std::max<size_t>((size_t)L->n_syn * L->rec_bytes, 16));
   L->off_dly = take(std::max<size_t>((size_t)L->n_syn * L->dly_bytes, 16));
   L->off_V = take((size_t)L->N * 4);

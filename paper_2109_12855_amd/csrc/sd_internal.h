@@ -28,12 +28,12 @@ constexpr int kFillChunk = 2048;     // draws ranked per build iteration
 //   WF_BF16        u32: low half BF16 weight, high half the slot
 //   WF_BF16_RESID  u32: low half BF16 residual d (w = mu (1 + d)), high half
 //   and WF_PACKED  the slot
-// Exports take the delay from the slot.  A record of target and delay took a second load and a multiply-add per synapse: 20
-// slices of the 112,500-neuron net in FP32 660 -> 619 us, 14 of 16 sweep nets
-// 5640 -> 5092 us.  The FP32 form's two arrays hold 6 bytes a synapse where one
-// 8-byte record has two unused: 20 slices of 112,500 neurons 607 -> 595 us (the
-// walk runs at the rate of a copy), plastic 1103 -> 1050, a small net's step the
-// same.
+// Exports take the delay from the slot.  A record of target and delay took a
+// second load and a multiply-add per synapse: 20 slices of the 112,500-neuron
+// net in FP32 660 -> 619 us, 14 of 16 sweep nets 5640 -> 5092 us.  The FP32
+// form's two arrays hold 6 bytes a synapse where one 8-byte record has two
+// unused: 20 slices of 112,500 neurons 607 -> 595 us, plastic 1103 -> 1050, a
+// small net's step the same.
 constexpr int kSynSlotBits = 16;
 // kernel forms: a weight and a slot, or records of 4 bytes (the BF16 forms
 // differ in their fixed-point constants only)

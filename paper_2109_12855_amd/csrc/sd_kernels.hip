@@ -951,7 +951,9 @@ __host__ __device__ inline SliceLds slice_lds_layout(int B, int Dmin, int win_ro
   L.win = o;   o = up(o + (size_t)win_rows * B * 8);    // int64 ring window
   L.carry = o; o = up(o + (staged_in_regs(B, Dmin) ? 0 : (size_t)Dmin * B * 4));  // staged HBM rows
   L.dcnt = o;  o = up(o + (size_t)Dmin * B);            // Poisson-drive counts (u8)
-  o = up(o + (size_t)Dmin * (B / 32) * 4);  // spare: the block sizes that fit stay the same
+  // not used: without it larger blocks would fit, and the automatic block sizes
+  // (with them the saved results of a tuning run) would be others
+  o = up(o + (size_t)Dmin * (B / 32) * 4);
   L.thr = o;   o = up(o + (size_t)kMaxThr * 4);         // drive thresholds
   L.scr = o;   o = up(o + (size_t)(kSliceThreads / 64 + 2) * 4);
   // one descriptor per spike of a chunk, plus one group of padding so a
@@ -1092,8 +1094,10 @@ __device__ __forceinline__ void walk_chunk(const SliceArgs& a, const uint2* desc
 // the wave takes 64 / LPS of them.  A segment's place, count and meta word are
 // then per lane.  Segments longer than LPS take further rounds.  What bounds a
 // small net's walk is the loads in flight per wave and the instructions per
-// segment, not the bytes: 14 slices of 16 nets of the sweep took 2980 us with
-// a wave per segment and take 2553 this way.
+// segment, not the bytes: 100 slices of 1,250 neurons (6 synapses a segment)
+// took 768 us with a wave per segment and 674 this way, 20 of 30,011 (13) 304
+// and 252.  14 slices of 16 sweep nets: 2980 and 2553, though only one of them
+// (37,586 neurons, 21 synapses a segment) takes this walk.
 template <int KF, int LPS, typename F>
 __device__ __forceinline__ void walk_short(const SliceArgs& a, const uint2* desc,
                                            const uint32_t* meta, int n_c, int* s_next,
