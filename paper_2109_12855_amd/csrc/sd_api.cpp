@@ -202,10 +202,11 @@ hipError_t launcher_run(SliceLauncher& L, hipStream_t s, const sd::SliceArgs* li
 
 constexpr int32_t kPersistAuto = -1;
 // A cooperative launch costs ~20 us more than an ordinary one and a slice in
-// it 5 to 12 us less.  At 4 slices (us, one launch per slice against
-// persistent): 1,250-neuron delta net 59.8 / 59.5, 30,011 alpha 90 / 88,
-// 112,500 packed 130 / 119, one-step slices 82 / 68; at 3 slices 45 / 50,
-// 69 / 74, 98 / 98, 61 / 59.
+// it 5 to 10 us less.  At 4 slices (us, one launch per slice against
+// persistent): 1,250-neuron delta net 54.3 / 49.1, 30,011 alpha 78.3 / 69.9,
+// 112,500 packed 119.6 / 113.5, FP32 134.6 / 132.3, one-step slices 86.1 /
+// 71.2; at 3 slices 43.7 / 43.9, 62.8 / 63.0, 88.1 / 91.8, 100.1 / 102.8,
+// 68.4 / 61.0.
 constexpr int64_t kPersistAutoMin = 4;
 constexpr int64_t kPersistAutoMax = 1024;  // slices of one launch
 // a wait lasts as long as another stream's kernel keeps a block off its

@@ -1992,9 +1992,10 @@ __global__ void __launch_bounds__(kSliceThreads) k_slice1(SingleArgs s) {
 // after its last read of this one.  Spikes past a line's capacity go to the
 // block's part of the slice's list buffer, between a release and an acquire
 // fence.
-// Per slice, one launch per slice against this kernel (stretches of 20 to 100
-// slices): 1,250-neuron delta net 14.9 -> 6.7 us, 30,011 alpha neurons 22.5 ->
-// 11, 112,500 packed 32.8 -> 22, FP32 37.6 -> 24, one-step slices 20.5 -> 8.7.
+// Per slice, one launch per slice against this kernel (stretches of 100
+// slices): 1,250-neuron delta net 10.9 -> 6.4 us, 30,011 alpha neurons 17.0 ->
+// 9.7, 112,500 packed 28.9 -> 21.9, FP32 30.3 -> 24.0, one-step slices 19.0 ->
+// 8.7.
 // Three polls in flight instead of one were 2% slower, spike groups split
 // evenly over the waves 1-3%.
 constexpr int64_t kBarSpin = 1LL << 22;  // polls before a wait gives up (explicit mode)
